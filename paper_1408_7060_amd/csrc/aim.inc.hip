@@ -1981,81 +1981,6 @@ __global__ void k_excitation(zd* __restrict__ V, const double* __restrict__ Sq, 
     }
 }
 
-// Far-field operator taps F[tap][d][x][k] (complex128):
-//   -(mu/4pi) [I - d d] sum_q Sq[k][q] [T'(tau)/dt + j w T(tau)] exp(j kc d.r_q),
-//   tau = (m_lo + tap) + d.r_q/(c dt).
-__global__ void k_farfield_taps(zd* __restrict__ F, const double* __restrict__ Sq, const double* __restrict__ rq,
-                                const double* __restrict__ dirs, int nd, int ns, int ntap, int m_lo, double dt,
-                                double w, double mu4pi, TBasis tb) {
-    const size_t tot = (size_t)ntap * nd * ns;
-    const double kc = w / kC0, cdt = kC0 * dt;
-    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < tot; e += (size_t)gridDim.x * blockDim.x) {
-        const int k = (int)(e % ns);
-        const int d = (int)((e / ns) % nd);
-        const int tap = (int)(e / ((size_t)ns * nd));
-        const double* u = dirs + 3 * d;
-        double acc[3][2] = {{0, 0}, {0, 0}, {0, 0}};
-        for (int q = 0; q < 14; ++q) {
-            const double* S = Sq + ((size_t)k * 14 + q) * 3;
-            const double* r = rq + ((size_t)k * 14 + q) * 3;
-            const double dr = r[0] * u[0] + r[1] * u[1] + r[2] * u[2];
-            double T[4];
-            if (!tb.eval((double)(m_lo + tap) + dr / cdt, T)) continue;
-            const double c = cos(kc * dr), s = sin(kc * dr);
-            // (T'/dt + j w T) (c + j s)
-            const double fr = T[1] / dt * c - w * T[0] * s;
-            const double fi = T[1] / dt * s + w * T[0] * c;
-            for (int x = 0; x < 3; ++x) {
-                acc[x][0] += S[x] * fr;
-                acc[x][1] += S[x] * fi;
-            }
-        }
-        // transverse projection and scale
-        const double pr = u[0] * acc[0][0] + u[1] * acc[1][0] + u[2] * acc[2][0];
-        const double pi = u[0] * acc[0][1] + u[1] * acc[1][1] + u[2] * acc[2][1];
-        for (int x = 0; x < 3; ++x) {
-            const double vr = acc[x][0] - u[x] * pr, vi = acc[x][1] - u[x] * pi;
-            F[(((size_t)tap * nd + d) * 3 + x) * ns + k] = zd{-mu4pi * vr, -mu4pi * vi};
-        }
-    }
-}
-
-// U[l][b][d][x] = sum_tap sum_k F[tap][d][x][k] I[l - (m_lo+tap)][b][k]; block per output.
-__global__ void __launch_bounds__(256) k_farfield_apply(zd* __restrict__ U, const zd* __restrict__ F,
-                                                        const zd* __restrict__ I, int nt, int B, int nd, int ns,
-                                                        int ntap, int m_lo) {
-    __shared__ double sh[256];
-    const int o = blockIdx.x;  // ((l*B + b)*nd + d)*3 + x
-    const int x = o % 3, d = (o / 3) % nd, b = (o / (3 * nd)) % B, l = o / (3 * nd * B);
-    double re = 0, im = 0;
-    for (int tap = 0; tap < ntap; ++tap) {
-        const int j = l - (m_lo + tap);
-        if (j < 0 || j >= nt) continue;
-        const zd* f = F + (((size_t)tap * nd + d) * 3 + x) * ns;
-        const zd* v = I + ((size_t)j * B + b) * ns;
-        for (int k = threadIdx.x; k < ns; k += 256) {
-            re += f[k].x * v[k].x - f[k].y * v[k].y;
-            im += f[k].x * v[k].y + f[k].y * v[k].x;
-        }
-    }
-    sh[threadIdx.x] = re;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    const double rs = sh[0];
-    __syncthreads();
-    sh[threadIdx.x] = im;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) U[o] = zd{rs, sh[0]};
-}
-
-// S[j][b][k] = sum_tap sum_{d,x} conj(F[tap][d][x][k]) U[j + m_lo + tap][b][d][x]
 // Co-polarised RCS from far-field envelopes (Sec. 2.4), one thread per
 // (frequency i, incidence b, direction d): the envelope's Fourier transform
 // at df[i] (samples at t = (l+1) dt), projected on pol[d], over the incident
@@ -2080,29 +2005,6 @@ __global__ void k_rcs(double* __restrict__ out, const zd* __restrict__ U, const 
         }
         const double a2 = (acc.x * acc.x + acc.y * acc.y) * dt * dt;
         out[e] = 4.0 * kPi * a2 / (G[i] * G[i]);
-    }
-}
-
-__global__ void k_farfield_adjoint(zd* __restrict__ S, const zd* __restrict__ F, const zd* __restrict__ U, int nt,
-                                   int B, int nd, int ns, int ntap, int m_lo) {
-    const size_t tot = (size_t)nt * B * ns;
-    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < tot; e += (size_t)gridDim.x * blockDim.x) {
-        const int k = (int)(e % ns);
-        const int b = (int)((e / ns) % B);
-        const int j = (int)(e / ((size_t)ns * B));
-        double re = 0, im = 0;
-        for (int tap = 0; tap < ntap; ++tap) {
-            const int l = j + m_lo + tap;
-            if (l < 0 || l >= nt) continue;
-            for (int d = 0; d < nd; ++d)
-                for (int x = 0; x < 3; ++x) {
-                    const zd f = F[(((size_t)tap * nd + d) * 3 + x) * ns + k];
-                    const zd u = U[(((size_t)l * B + b) * nd + d) * 3 + x];
-                    re += f.x * u.x + f.y * u.y;
-                    im += f.x * u.y - f.y * u.x;
-                }
-        }
-        S[e] = zd{re, im};
     }
 }
 

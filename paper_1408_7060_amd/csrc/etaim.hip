@@ -17,6 +17,7 @@
 
 #include "aim.inc.hip"
 #include "context.hpp"
+#include "farfield.inc.hip"
 #include "krylov.inc.hip"
 
 using namespace etaim;
@@ -161,6 +162,8 @@ struct etaim_ctx {
     int guess_order = kMaxGuess;  // solutions extrapolated into a step's initial guess (0..kMaxGuess)
     int x_engine = 0;   // 0: LDS line kernels, 1: register line kernels
     void* xs = nullptr; // [ns][B] scaled columns for the register anterpolation
+    void* farws = nullptr;  // far-field work space (tap table, partial sums), kept between calls up to kFarKeep
+    size_t farws_bytes = 0;
     hipEvent_t ev[8] = {};  // march phase events, two sets (steps alternate)
     hipEvent_t evg[2] = {}; // around a run of replayed whole-step graphs
     // FP64 residual check of an FP32 march (ETAIM_F_RESIDUAL_CHECK): an FP64
@@ -218,6 +221,7 @@ struct etaim_ctx {
         if (sctl_h) (void)hipHostFree(sctl_h);
         if (cap_stream) (void)hipStreamDestroy(cap_stream);
         for (void* p : allocs) (void)hipFree(p);
+        if (farws) (void)hipFree(farws);
     }
 };
 
@@ -2852,22 +2856,183 @@ void etaim_destroy(etaim_ctx* c) {
 }  // extern "C"
 
 namespace {
-int farfield_taps(etaim_ctx* c, int nd, const double* dirs, zd*& F, double*& dd, int& ntap, int& m_lo) {
-    double rad = 0;
-    for (double v : c->geo.xyz) rad = std::max(rad, std::fabs(v));
-    const double smax = rad * std::sqrt(3.0) / (kC0 * c->st.dt);
-    m_lo = (int)std::floor(c->st.tb.lo() - smax);
-    const int m_hi = (int)std::ceil(c->st.tb.hi() + smax);
-    ntap = m_hi - m_lo + 1;
-    std::vector<double> dv(dirs, dirs + 3 * (size_t)nd);
-    CHK(c->upload(dd, dv));
-    CHK(c->alloc(F, (size_t)ntap * nd * 3 * c->ns));
-    const size_t tot = (size_t)ntap * nd * c->ns;
-    hipLaunchKernelGGL(k_farfield_taps, dim3(blocks_for(tot)), dim3(256), 0, c->stream, F, c->Sq, c->rq, dd, nd,
-                       c->ns, ntap, m_lo, c->st.dt, 2.0 * kPi * c->prm.fc, kMu0 / (4.0 * kPi), c->st.tb);
+// Directions of one far-field call, in groups whose tap table stays within
+// kFarTable bytes: a group's table is read once per row tile and is to stay in
+// the last-level cache (256 MB) between its readers.
+constexpr size_t kFarTable = (size_t)224 << 20;
+// far-field work space a context keeps between calls (a larger one is freed
+// when the call ends)
+constexpr size_t kFarKeep = (size_t)320 << 20;
+// blocks a product is split into at most: two rounds of the two that fit each
+// of 256 compute units (more, smaller ones write more partial sums)
+constexpr int kFarBlocks = 1024;
+
+struct FarPlan {
+    int nc = 2, ntap = 0, m_lo = 0, group = 0, M = 0;
+    std::vector<double> geo, q;  // per direction: {d, P_0, P_1, P_2}, {Q_0, Q_1, Q_2}
+};
+
+void far_plan(const etaim_ctx* c, int nd, const double* dirs, FarPlan& f) {
+    f.M = c->prm.nt_steps * c->B;
+    for (int d = 0; d < nd; ++d) {
+        const double* u = dirs + 3 * (size_t)d;
+        if (!(std::fabs(u[0] * u[0] + u[1] * u[1] + u[2] * u[2] - 1.0) < 1e-12)) f.nc = 3;
+    }
+    // |d.r| is at most the largest vertex distance from the origin for unit
+    // directions (27 taps on the unit sphere at N_g = 24); other directions
+    // keep the range of the cube around the object
+    double r2 = 0, rad = 0;
+    for (int i = 0; i < c->geo.nv; ++i) {
+        const double* v = &c->geo.xyz[3 * (size_t)i];
+        r2 = std::max(r2, v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+        for (int x = 0; x < 3; ++x) rad = std::max(rad, std::fabs(v[x]));
+    }
+    const double reach = f.nc == 2 ? std::sqrt(r2) * (1.0 + 1e-9) : rad * std::sqrt(3.0);
+    const double smax = reach / (kC0 * c->st.dt);
+    f.m_lo = (int)std::floor(c->st.tb.lo() - smax);
+    f.ntap = (int)std::ceil(c->st.tb.hi() + smax) - f.m_lo + 1;
+    f.geo.assign(12 * (size_t)nd, 0.0);
+    f.q.assign(9 * (size_t)nd, 0.0);
+    for (int d = 0; d < nd; ++d) {
+        const double* u = dirs + 3 * (size_t)d;
+        double* g = &f.geo[12 * (size_t)d];
+        double* q = &f.q[9 * (size_t)d];
+        for (int x = 0; x < 3; ++x) g[x] = u[x];
+        if (f.nc == 3) {
+            for (int x = 0; x < 3; ++x) {
+                for (int y = 0; y < 3; ++y) g[3 + 3 * x + y] = (x == y ? 1.0 : 0.0) - u[x] * u[y];
+                q[3 * x + x] = 1.0;
+            }
+            continue;
+        }
+        // e1 = d x a / |d x a|, a the axis d is furthest from; e2 = d x e1
+        int ax = 0;
+        for (int x = 1; x < 3; ++x)
+            if (std::fabs(u[x]) < std::fabs(u[ax])) ax = x;
+        double a[3] = {0, 0, 0}, *e1 = g + 3, *e2 = g + 6;
+        a[ax] = 1.0;
+        auto cross = [](const double* p, const double* r, double* o) {
+            for (int x = 0; x < 3; ++x) o[x] = p[(x + 1) % 3] * r[(x + 2) % 3] - p[(x + 2) % 3] * r[(x + 1) % 3];
+        };
+        cross(u, a, e1);
+        const double n = std::sqrt(e1[0] * e1[0] + e1[1] * e1[1] + e1[2] * e1[2]);
+        for (int x = 0; x < 3; ++x) e1[x] /= n;
+        cross(u, e1, e2);
+        for (int x = 0; x < 6; ++x) q[x] = g[3 + x];
+    }
+    // whole column tiles per group where the table allows it
+    const size_t per = (size_t)f.ntap * f.nc * c->ns * sizeof(zd);
+    int grp = (int)std::min<size_t>({std::max<size_t>(kFarTable / per, 1), (size_t)nd, (size_t)32768});
+    const int tile = kFarTile / (f.nc == 2 ? 2 : 1);
+    if (grp < nd && grp > tile) grp -= grp % tile;
+    f.group = grp;
+}
+
+int far_tiles(int n) { return (n + kFarTile - 1) / kFarTile; }
+// blocks a product's steps are split over
+int far_splits(int M, int N, int K, int ntap) {
+    const long long tiles = (long long)far_tiles(M) * far_tiles(N);
+    const long long steps = (long long)((K + kFarK - 1) / kFarK) * ntap;
+    return (int)std::max(1LL, std::min(kFarBlocks / tiles, steps / 4));
+}
+
+// one group's product: part[nsplit][M][N] (or out directly with nsplit = 1)
+template <bool ADJ>
+int far_gemm(etaim_ctx* c, const zd* A, const zd* F, zd* out, const FarPlan& f, int N, int K, int nsplit, int add) {
+    const int mt = far_tiles(f.M), nt = far_tiles(N);
+    const long long blocks = (long long)mt * nt * nsplit;
+    if (blocks > 0x7ffffff0LL) return fail(ETAIM_EUNSUPPORTED, "far field: too many rows for one launch");
+    hipLaunchKernelGGL(k_far_gemm<ADJ>, dim3((unsigned)((blocks + kXcds - 1) / kXcds * kXcds)), dim3(256), 0, c->stream,
+                       A, F, out, f.M, N, K, f.ntap, f.m_lo, c->B, mt, nt, nsplit, add);
     HIPCHK(hipGetLastError());
     return ETAIM_OK;
 }
+
+// the tap table of directions d0 .. d0 + n - 1
+int far_taps(etaim_ctx* c, const FarPlan& f, zd* F, const double* geo, int d0, int n) {
+    const dim3 grid((unsigned)((c->ns + 127) / 128), (unsigned)n);
+    const double w = 2.0 * kPi * c->prm.fc, mu4pi = kMu0 / (4.0 * kPi);
+#define ETAIM_TAPS(NC, BL)                                                                                          \
+    hipLaunchKernelGGL((k_far_taps<NC, BL>), grid, dim3(128), 0, c->stream, F, c->Sq, c->rq, geo + 12 * (size_t)d0, \
+                       n, c->ns, f.ntap, f.m_lo, c->st.dt, w, mu4pi, c->st.tb)
+    if (f.nc == 2) {
+        if (c->st.tb.kind) ETAIM_TAPS(2, true); else ETAIM_TAPS(2, false);
+    } else {
+        if (c->st.tb.kind) ETAIM_TAPS(3, true); else ETAIM_TAPS(3, false);
+    }
+#undef ETAIM_TAPS
+    HIPCHK(hipGetLastError());
+    return ETAIM_OK;
+}
+
+// far-field work space of at least `bytes` (kept between calls up to kFarKeep)
+int far_space(etaim_ctx* c, size_t bytes) {
+    if (c->farws_bytes >= bytes) return ETAIM_OK;
+    if (c->farws) HIPCHK(hipFree(c->farws));
+    c->farws = nullptr;
+    c->farws_bytes = 0;
+    if (hipMalloc(&c->farws, bytes) != hipSuccess)
+        return fail(ETAIM_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+    c->farws_bytes = bytes;
+    return ETAIM_OK;
+}
+
+// U = F I (adj false) or S = F^H U (adj true) over the direction groups
+int far_run(etaim_ctx* c, int nd, const double* dirs, const zd* in, zd* out, bool adj) {
+    FarPlan f;
+    far_plan(c, nd, dirs, f);
+    const int ns = c->ns, colmax = f.group * f.nc;
+    auto up = [](size_t b) { return (b + 255) / 256 * 256; };
+    auto splits = [&](int n) {
+        return adj ? far_splits(f.M, ns, n * f.nc, f.ntap) : far_splits(f.M, n * f.nc, ns, f.ntap);
+    };
+    // the last group may be smaller and split finer
+    auto part_bytes = [&](int n) {
+        const int s = splits(n);
+        return adj && s == 1 ? (size_t)0 : (size_t)s * f.M * (adj ? ns : n * f.nc) * sizeof(zd);
+    };
+    const int last = nd % f.group ? nd % f.group : f.group;
+    const size_t bF = up((size_t)f.ntap * colmax * ns * sizeof(zd)), bP = up(std::max(part_bytes(f.group), part_bytes(last))),
+                 bW = adj ? up((size_t)f.M * colmax * sizeof(zd)) : 0, bG = up(21 * (size_t)nd * sizeof(double));
+    CHK(far_space(c, bF + bP + bW + bG));
+    char* p = (char*)c->farws;
+    zd *F = (zd*)p, *part = (zd*)(p + bF), *W = (zd*)(p + bF + bP);
+    double* geo = (double*)(p + bF + bP + bW);
+    double* q = geo + 12 * (size_t)nd;
+    f.geo.insert(f.geo.end(), f.q.begin(), f.q.end());
+    HIPCHK(hipMemcpyAsync(geo, f.geo.data(), f.geo.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
+    for (int d0 = 0; d0 < nd; d0 += f.group) {
+        const int n = std::min(f.group, nd - d0), cols = n * f.nc, s = splits(n);
+        CHK(far_taps(c, f, F, geo, d0, n));
+        if (!adj) {
+            CHK(far_gemm<false>(c, in, F, part, f, cols, ns, s, 0));
+            const size_t np = (size_t)f.M * cols;
+            if (s > 1)
+                hipLaunchKernelGGL(k_far_reduce, dim3((unsigned)((np + 31) / 32)), dim3(256), 0, c->stream, part, np, s);
+            hipLaunchKernelGGL(k_far_expand, dim3((unsigned)(((size_t)f.M * n + 255) / 256)), dim3(256), 0, c->stream, out,
+                               part, q + 9 * (size_t)d0, f.M, n, f.nc, nd, d0);
+        } else {
+            const size_t nw = (size_t)f.M * cols, no = (size_t)f.M * ns;
+            hipLaunchKernelGGL(k_far_project, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, c->stream, W, in,
+                               q + 9 * (size_t)d0, f.M, n, f.nc, nd, d0);
+            const int add = d0 > 0 ? 1 : 0;
+            CHK(far_gemm<true>(c, W, F, s == 1 ? out : part, f, ns, cols, s, s == 1 ? add : 0));
+            if (s > 1)
+                hipLaunchKernelGGL(k_far_sum, dim3((unsigned)((no + 31) / 32)), dim3(256), 0, c->stream, out, part, no, s,
+                                   add);
+        }
+        HIPCHK(hipGetLastError());
+    }
+    // the direction arrays on the host and the work space are free after this
+    HIPCHK(hipStreamSynchronize(c->stream));
+    if (c->farws_bytes > kFarKeep) {
+        HIPCHK(hipFree(c->farws));
+        c->farws = nullptr;
+        c->farws_bytes = 0;
+    }
+    return ETAIM_OK;
+}
+
 int release_last(etaim_ctx* c, int n) {
     for (int i = 0; i < n && !c->allocs.empty(); ++i) {
         HIPCHK(hipFree(c->allocs.back()));
@@ -2881,39 +3046,13 @@ extern "C" {
 int etaim_farfield(etaim_ctx* c, int32_t nd, const double* dirs, const void* I, void* U) {
     CHK(check_ctx(c));
     if (nd < 1 || !dirs || !I || !U) return fail(ETAIM_EINVAL, "farfield needs nd >= 1, dirs, I and U");
-    zd* F = nullptr;
-    double* dd = nullptr;
-    int ntap = 0, m_lo = 0;
-    HIPCHK(hipStreamSynchronize(c->stream));
-    const int64_t before = c->dev_bytes;
-    CHK(farfield_taps(c, nd, dirs, F, dd, ntap, m_lo));
-    const int nout = c->prm.nt_steps * c->B * nd * 3;
-    hipLaunchKernelGGL(k_farfield_apply, dim3(nout), dim3(256), 0, c->stream, (zd*)U, F, (const zd*)I,
-                       c->prm.nt_steps, c->B, nd, c->ns, ntap, m_lo);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipStreamSynchronize(c->stream));
-    CHK(release_last(c, 2));
-    c->dev_bytes = before;
-    return ETAIM_OK;
+    return far_run(c, nd, dirs, (const zd*)I, (zd*)U, false);
 }
 
 int etaim_farfield_adjoint(etaim_ctx* c, int32_t nd, const double* dirs, const void* Ubar, void* S) {
     CHK(check_ctx(c));
     if (nd < 1 || !dirs || !Ubar || !S) return fail(ETAIM_EINVAL, "farfield_adjoint needs nd >= 1, dirs, Ubar, S");
-    zd* F = nullptr;
-    double* dd = nullptr;
-    int ntap = 0, m_lo = 0;
-    HIPCHK(hipStreamSynchronize(c->stream));
-    const int64_t before = c->dev_bytes;
-    CHK(farfield_taps(c, nd, dirs, F, dd, ntap, m_lo));
-    const size_t tot = (size_t)c->prm.nt_steps * c->B * c->ns;
-    hipLaunchKernelGGL(k_farfield_adjoint, dim3(blocks_for(tot)), dim3(256), 0, c->stream, (zd*)S, F,
-                       (const zd*)Ubar, c->prm.nt_steps, c->B, nd, c->ns, ntap, m_lo);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipStreamSynchronize(c->stream));
-    CHK(release_last(c, 2));
-    c->dev_bytes = before;
-    return ETAIM_OK;
+    return far_run(c, nd, dirs, (const zd*)Ubar, (zd*)S, true);
 }
 
 int etaim_rcs(etaim_ctx* c, int32_t nd, const double* pol, int32_t nf, const double* df, double pulse_sigma,
