@@ -48,6 +48,8 @@ int fail(int code, const std::string& msg) {
 constexpr int kLdsBudget = 64 * 1024;
 // largest grid y dimension of a launch
 constexpr size_t kMaxGridY = 65535;
+// most blocks of 256 threads of a launch (fewer than 2^32 threads)
+constexpr size_t kMaxBlocks256 = ((size_t)1 << 24) - 8;
 // batches up to this many columns apply the preconditioner with lane groups per row
 constexpr int kSpmvGroupMaxB = 4;
 // most blocks one dot product or norm is split over
@@ -2396,6 +2398,31 @@ double* scratch_of(int dev) {
 }
 }  // namespace
 
+namespace {
+// steps one excitation thread takes at most: past 32 the set-up of its 14
+// points no longer shows beside their exponentials
+constexpr size_t kExcSteps = 32;
+// threads the excitation is spread over before a thread takes several steps
+// (a quarter of what the card holds; few steps of a small problem stay spread)
+constexpr size_t kExcThreads = 131072;
+
+// V from the directions and polarisations kp [2][nb][3] on the device
+int excitation_launch(etaim_ctx* c, int nb, const double* kp, double sigma, double td, zd* V) {
+    const size_t nt = (size_t)c->prm.nt_steps, tot = nt * nb * c->ns;
+    const size_t cols = (size_t)((c->ns + 255) / 256) * nb;
+    size_t lc = std::max<size_t>(1, std::min(kExcSteps, tot / kExcThreads));
+    // a launch holds fewer than 2^32 threads
+    lc = std::max(lc, (cols * nt + kMaxBlocks256 - 1) / kMaxBlocks256);
+    const size_t blocks = cols * ((nt + lc - 1) / lc);
+    if (blocks > kMaxBlocks256) return fail(ETAIM_EUNSUPPORTED, "excitation: too many steps and directions for one launch");
+    hipLaunchKernelGGL(k_excitation, dim3((unsigned)blocks), dim3(256), 0, c->stream, V, c->Sq, c->rq, kp,
+                       kp + 3 * (size_t)nb, (int)nt, nb, c->ns, (int)lc, c->st.dt, sigma, td, 2.0 * kPi * c->prm.fc,
+                       (const double*)c->Snq, c->st.alpha);
+    HIPCHK(hipGetLastError());
+    return ETAIM_OK;
+}
+}  // namespace
+
 // ===========================================================================
 extern "C" {
 
@@ -2501,11 +2528,7 @@ int etaim_excitation_planewave(etaim_ctx* c, int32_t nb, const double* khat, con
     std::memcpy(kp.data() + 3 * nb, phat, 3 * nb * sizeof(double));
     double* d = nullptr;
     CHK(c->upload(d, kp));
-    const size_t tot = (size_t)c->prm.nt_steps * nb * c->ns;
-    hipLaunchKernelGGL(k_excitation, dim3(blocks_for(tot)), dim3(256), 0, c->stream, (zd*)V, c->Sq, c->rq, d,
-                       d + 3 * nb, c->prm.nt_steps, nb, c->ns, c->st.dt, sigma, td, 2.0 * kPi * c->prm.fc,
-                       (const double*)c->Snq, c->st.alpha);
-    HIPCHK(hipGetLastError());
+    CHK(excitation_launch(c, nb, d, sigma, td, (zd*)V));
     HIPCHK(hipStreamSynchronize(c->stream));
     c->allocs.pop_back();
     c->dev_bytes -= (int64_t)(kp.size() * sizeof(double));
@@ -2526,11 +2549,7 @@ int etaim_excitation_planewave_noalloc(etaim_ctx* c, int32_t nb, const double* k
     HIPCHK(hipMemcpyAsync(d, khat, 3 * (size_t)nb * sizeof(double), hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(d + 3 * (size_t)nb, phat, 3 * (size_t)nb * sizeof(double), hipMemcpyHostToDevice,
                           c->stream));
-    const size_t tot = (size_t)c->prm.nt_steps * nb * c->ns;
-    hipLaunchKernelGGL(k_excitation, dim3(blocks_for(tot)), dim3(256), 0, c->stream, (zd*)V, c->Sq, c->rq, d,
-                       d + 3 * (size_t)nb, c->prm.nt_steps, nb, c->ns, c->st.dt, sigma, td, 2.0 * kPi * c->prm.fc,
-                       (const double*)c->Snq, c->st.alpha);
-    HIPCHK(hipGetLastError());
+    CHK(excitation_launch(c, nb, d, sigma, td, (zd*)V));
     // the staging is free for the next call (and the caller's host arrays) once this returns
     HIPCHK(hipStreamSynchronize(c->stream));
     return ETAIM_OK;
@@ -2941,7 +2960,7 @@ template <bool ADJ>
 int far_gemm(etaim_ctx* c, const zd* A, const zd* F, zd* out, const FarPlan& f, int N, int K, int nsplit, int add) {
     const int mt = far_tiles(f.M), nt = far_tiles(N);
     const long long blocks = (long long)mt * nt * nsplit;
-    if (blocks > 0x7ffffff0LL) return fail(ETAIM_EUNSUPPORTED, "far field: too many rows for one launch");
+    if (blocks > (long long)kMaxBlocks256) return fail(ETAIM_EUNSUPPORTED, "far field: too many rows for one launch");
     hipLaunchKernelGGL(k_far_gemm<ADJ>, dim3((unsigned)((blocks + kXcds - 1) / kXcds * kXcds)), dim3(256), 0, c->stream,
                        A, F, out, f.M, N, K, f.ntap, f.m_lo, c->B, mt, nt, nsplit, add);
     HIPCHK(hipGetLastError());
@@ -3009,11 +3028,11 @@ int far_run(etaim_ctx* c, int nd, const double* dirs, const zd* in, zd* out, boo
             const size_t np = (size_t)f.M * cols;
             if (s > 1)
                 hipLaunchKernelGGL(k_far_reduce, dim3((unsigned)((np + 31) / 32)), dim3(256), 0, c->stream, part, np, s);
-            hipLaunchKernelGGL(k_far_expand, dim3((unsigned)(((size_t)f.M * n + 255) / 256)), dim3(256), 0, c->stream, out,
+            hipLaunchKernelGGL(k_far_expand, dim3(blocks_for((size_t)f.M * n)), dim3(256), 0, c->stream, out,
                                part, q + 9 * (size_t)d0, f.M, n, f.nc, nd, d0);
         } else {
             const size_t nw = (size_t)f.M * cols, no = (size_t)f.M * ns;
-            hipLaunchKernelGGL(k_far_project, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, c->stream, W, in,
+            hipLaunchKernelGGL(k_far_project, dim3(blocks_for(nw)), dim3(256), 0, c->stream, W, in,
                                q + 9 * (size_t)d0, f.M, n, f.nc, nd, d0);
             const int add = d0 > 0 ? 1 : 0;
             CHK(far_gemm<true>(c, W, F, s == 1 ? out : part, f, ns, cols, s, s == 1 ? add : 0));

@@ -283,27 +283,29 @@ __global__ void __launch_bounds__(256) k_far_reduce(zd* __restrict__ part, size_
 __global__ void __launch_bounds__(256) k_far_expand(zd* __restrict__ U, const zd* __restrict__ part,
                                                     const double* __restrict__ q, int M, int nd, int nc, int ndt,
                                                     int d0) {
-    const size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    if (e >= (size_t)M * nd) return;
-    const size_t r = e / nd;
-    const int d = (int)(e - r * nd);
-    zd o[3] = {{0, 0}, {0, 0}, {0, 0}};
-    for (int c = 0; c < nc; ++c)
-        for (int x = 0; x < 3; ++x) o[x] += q[9 * (size_t)d + 3 * c + x] * part[(r * nd + d) * nc + c];
-    for (int x = 0; x < 3; ++x) U[(r * ndt + d0 + d) * 3 + x] = o[x];
+    const size_t tot = (size_t)M * nd;
+    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < tot; e += (size_t)gridDim.x * blockDim.x) {
+        const size_t r = e / nd;
+        const int d = (int)(e - r * nd);
+        zd o[3] = {{0, 0}, {0, 0}, {0, 0}};
+        for (int c = 0; c < nc; ++c)
+            for (int x = 0; x < 3; ++x) o[x] += q[9 * (size_t)d + 3 * c + x] * part[(r * nd + d) * nc + c];
+        for (int x = 0; x < 3; ++x) U[(r * ndt + d0 + d) * 3 + x] = o[x];
+    }
 }
 
 // W[r][d nc + c] = sum_x Q[d][c][x] U[r][d0 + d][x]
 __global__ void __launch_bounds__(256) k_far_project(zd* __restrict__ W, const zd* __restrict__ U,
                                                      const double* __restrict__ q, int M, int nd, int nc, int ndt,
                                                      int d0) {
-    const size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    if (e >= (size_t)M * nd * nc) return;
-    const size_t r = e / ((size_t)nd * nc);
-    const int n = (int)(e - r * nd * nc), d = n / nc;
-    zd a{0, 0};
-    for (int x = 0; x < 3; ++x) a += q[9 * (size_t)d + 3 * (n - d * nc) + x] * U[(r * ndt + d0 + d) * 3 + x];
-    W[e] = a;
+    const size_t tot = (size_t)M * nd * nc;
+    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < tot; e += (size_t)gridDim.x * blockDim.x) {
+        const size_t r = e / ((size_t)nd * nc);
+        const int n = (int)(e - r * nd * nc), d = n / nc;
+        zd a{0, 0};
+        for (int x = 0; x < 3; ++x) a += q[9 * (size_t)d + 3 * (n - d * nc) + x] * U[(r * ndt + d0 + d) * 3 + x];
+        W[e] = a;
+    }
 }
 
 // S[e] = (or +=) sum_split part[split][e]
