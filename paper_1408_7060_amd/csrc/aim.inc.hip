@@ -154,6 +154,76 @@ __global__ void __launch_bounds__(256) k_anterp_nz(const cplx<R>* __restrict__ x
     for (int c = 0; c < 4; ++c) q[((size_t)b * 4 + c) * N3 + t] = acc[c];
 }
 
+// writes of a wave's lanes to LDS visible to its other lanes (the LDS
+// serves a wave's accesses in order)
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The same anterpolation for few columns: eight lanes per (node, column).
+// Each lane forms the products of one of eight entries at a time (the loads
+// of two rounds in flight); they change hands through LDS, so that lane g
+// adds one real number of the result (component g / 2, real or imaginary
+// part) over the entries in the order of the lane-per-column kernel: the same
+// sums, rounded alike.  One lane per (node, column) leaves a chain of up to
+// 25 groups of dependent loads on a nearly empty card: bound by latency,
+// 10.7 us (level-2 sphere, FP64), 38.4 us (4 m plate, FP64) and 14.3 us
+// (level-4 sphere, FP32); this kernel 4.7, 7.8 and 7.5 us.
+constexpr int kAnterpLanes = 8;
+template <typename R>
+__global__ void __launch_bounds__(256) k_anterp_grp(const cplx<R>* __restrict__ xs, const int* __restrict__ nodes,
+                                                    int nnodes, const int* __restrict__ nptr,
+                                                    const int* __restrict__ nk, const R* __restrict__ nw,
+                                                    cplx<R>* __restrict__ q, GridDims g, int B,
+                                                    const int* __restrict__ gate) {
+    if (gated_off(gate)) return;
+    // per group: 2 rounds x 8 entries x 8 products, rows of 9
+    constexpr int GL = kAnterpLanes, ROW = GL + 1;
+    __shared__ R sh[256 / GL][2 * GL * ROW];
+    const size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x, pr = e / GL;
+    const bool live = pr < (size_t)nnodes * B;
+    const int lane = (int)(e % GL);
+    const int j = live ? (int)(pr / B) : 0, b = live ? (int)(pr - (size_t)j * B) : 0;
+    const int Nx = g.N[0], Ny = g.N[1];
+    const size_t N3 = (size_t)Nx * Ny * g.N[2];
+    const int t = nodes[j], y = t % Ny, r = t / Ny, x = r % Nx, z = r / Nx;
+    const size_t n = (size_t)x + (size_t)Nx * ((size_t)y + (size_t)Ny * z);
+    R* mine = sh[threadIdx.x / GL];
+    const int p0 = live ? nptr[n] : 0, p1 = live ? nptr[n + 1] : 0;
+    R acc = 0;
+    // the wave's groups run the rounds of its longest node together
+    int rounds = (p1 - p0 + 2 * GL - 1) / (2 * GL);
+#pragma unroll
+    for (int o = GL; o < 64; o <<= 1) rounds = max(rounds, __shfl_xor(rounds, o, 64));
+    for (int i = 0, p = p0 + lane; i < rounds; ++i, p += 2 * GL) {
+        int k[2];
+        R w[2][4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const bool in = p + h * GL < p1;
+            k[h] = in ? nk[p + h * GL] : 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) w[h][c] = in ? nw[4 * (size_t)(p + h * GL) + c] : (R)0;
+        }
+        cplx<R> v[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) v[h] = xs[(size_t)k[h] * B + b];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                mine[(h * GL + lane) * ROW + 2 * c] = w[h][c] * v[h].x;
+                mine[(h * GL + lane) * ROW + 2 * c + 1] = w[h][c] * v[h].y;
+            }
+        wave_sync();
+#pragma unroll
+        for (int u = 0; u < 2 * GL; ++u) acc += mine[u * ROW + lane];
+        wave_sync();
+    }
+    if (live) reinterpret_cast<R*>(q + ((size_t)b * 4 + (lane >> 1)) * N3 + t)[lane & 1] = acc;
+}
+
 // Forward x transform of the zero-padded lines: A[bc][kx][z][y] =
 // sum_{x<N} q[bc][z][x][y] w_{2N}^{kx x}.  Lanes (2l, 2l+1) own line l =
 // (z, y) of one bc with parity p: kx = 2a + p is the N-point DFT of
@@ -1504,12 +1574,17 @@ __device__ __forceinline__ R wave_sum(R v) {
 // xr = the scaled columns dinv . x and hist the current history, both in
 // the working precision with the columns of one basis contiguous ([ns][B]).
 // Lane j of the wave owns stencil node j (and near-zone entries e0 + j,
-// e0 + j + 64, ...) for up to kInterpCols columns at once; the 64-lane sums
+// e0 + j + 64, ...) for up to NC columns at once; the 64-lane sums
 // of all columns then take one transposing butterfly (each exchange halves
 // the columns a lane carries) instead of one full reduction per column.
-constexpr int kInterpCols = 32;
-
-template <typename R>
+// The columns a wave carries, NC, follow the batch: 1, 4 or 32 (every
+// unused column costs its share of the butterfly and of the registers: with
+// 32 for every batch, 21.3 us for one column of the 4 m plate in FP64 and
+// 14.5 us for the level-4 sphere in FP32, with one 8.7 and 9.7 us).
+// In mode 0 with m = 0, val holds the entries of Z_0 alone (mv = 1): the
+// lanes of a row then read one run instead of every M_n + 1st value (level-4
+// sphere, 32 columns in FP32: 116 -> 105 us).
+template <typename R, int NC>
 __global__ void __launch_bounds__(256) k_interp_near(
     const cplx<R>* __restrict__ P, const R* __restrict__ lam, const int* __restrict__ i0,
     const int* __restrict__ order, GridDims g,
@@ -1542,11 +1617,11 @@ __global__ void __launch_bounds__(256) k_interp_near(
 #pragma unroll
     for (int c = 0; c < 4; ++c) w[c] = lam[(size_t)k * 256 + 64 * c + j];
     const int e0 = rowptr[k], e1 = mode >= 2 ? e0 : rowptr[k + 1];
-    for (int b0 = 0; b0 < B; b0 += kInterpCols) {
-        const int nb = min(kInterpCols, B - b0);
-        cplx<R> acc[kInterpCols];
+    for (int b0 = 0; b0 < B; b0 += NC) {
+        const int nb = min(NC, B - b0);
+        cplx<R> acc[NC];
 #pragma unroll
-        for (int bb = 0; bb < kInterpCols; ++bb) {
+        for (int bb = 0; bb < NC; ++bb) {
             acc[bb] = cplx<R>{0, 0};
             if (bb < nb) {
                 const cplx<R>* pb = P + (size_t)(b0 + bb) * 4 * N + node;
@@ -1604,13 +1679,13 @@ __global__ void __launch_bounds__(256) k_interp_near(
             nacc.x += __shfl_xor(nacc.x, o, 64);
             nacc.y += __shfl_xor(nacc.y, o, 64);
         }
-        // transposing butterfly over the top log2(kInterpCols) lane bits: after
+        // transposing butterfly over the top log2(NC) lane bits: after
         // the exchange over a bit a lane keeps half its partial sums, those of
         // the half its bit selects; the lower bits then pair up, and the GL
         // lanes GL bb + {0 .. GL - 1} hold the full sum of column bb
-        constexpr int GL = 64 / kInterpCols;
+        constexpr int GL = 64 / NC;
 #pragma unroll
-        for (int h = kInterpCols / 2, bit = 32; h >= 1; h >>= 1, bit >>= 1) {
+        for (int h = NC / 2, bit = 32; h >= 1; h >>= 1, bit >>= 1) {
             const bool up = (lane & bit) != 0;
 #pragma unroll
             for (int i = 0; i < h; ++i) {
@@ -1939,6 +2014,15 @@ __global__ void __launch_bounds__(64) k_precorrect(zd* __restrict__ val, const d
     }
 }
 
+// a / d correctly rounded, r = the rounded 1 / d: the product with r, then
+// two corrections by the exact remainder (the first leaves the quotient
+// within one unit in the last place, the second rounds it)
+__device__ __forceinline__ double quotient(double a, double d, double r) {
+    double q = a * r;
+    q = fma(fma(-q, d, a), r, q);
+    return fma(fma(-q, d, a), r, q);
+}
+
 // Plane-wave excitation, eq. (1) with (d/dt + j w) applied:
 // V[l][b][k] = sum_{half,q} (Sq . p) [g'(tau) + j w g(tau)] exp(-j w (r.k/c + td))
 // Sq[k][h][q][3]: quadrature-weighted basis values; rq: points.
@@ -1948,7 +2032,7 @@ __global__ void __launch_bounds__(64) k_precorrect(zd* __restrict__ val, const d
 // of the 14 points do not depend on the step and stay in registers.  Bound
 // by the 14 exponentials per value (FP64 issue).  With every step's thread
 // forming phases and projections again: 3256 us a call for 100 steps x 32
-// directions x 7680 bases; this kernel 605 us.
+// directions x 7680 bases; this kernel 606 us.
 __global__ void __launch_bounds__(256) k_excitation(zd* __restrict__ V, const double* __restrict__ Sq,
                                                     const double* __restrict__ rq, const double* __restrict__ khat,
                                                     const double* __restrict__ phat, int nt, int nb, int ns, int lc,
@@ -1964,7 +2048,7 @@ __global__ void __launch_bounds__(256) k_excitation(zd* __restrict__ V, const do
     const double* ph = phat + 3 * (size_t)b;
     const double hx = kh[1] * ph[2] - kh[2] * ph[1], hy = kh[2] * ph[0] - kh[0] * ph[2],
                  hz = kh[0] * ph[1] - kh[1] * ph[0];
-    double rk[14], pc[14], ps[14];
+    double rk[14], pr[14], c[14], sn[14];
 #pragma unroll
     for (int q = 0; q < 14; ++q) {
         const double* S = Sq + ((size_t)k * 14 + q) * 3;
@@ -1975,27 +2059,23 @@ __global__ void __launch_bounds__(256) k_excitation(zd* __restrict__ V, const do
             const double* Sn = Snq + ((size_t)k * 14 + q) * 3;
             proj = alpha * proj + (1.0 - alpha) * (Sn[0] * hx + Sn[1] * hy + Sn[2] * hz);
         }
-        double sn, cs;
-        sincos(w * (rk[q] + td), &sn, &cs);
-        pc[q] = proj * cs;
-        ps[q] = -(proj * sn);
+        pr[q] = proj;
+        const double arg = w * (rk[q] + td);
+        c[q] = cos(arg);
+        sn[q] = -sin(arg);
     }
-    const double s2 = sigma * sigma, d2 = 2.0 * s2, i2 = 1.0 / d2;
+    const double s2 = sigma * sigma, d2 = 2.0 * s2, i1 = 1.0 / s2, i2 = 1.0 / d2;
     for (int l = l0; l < l1; ++l) {
         const double t = (double)(l + 1) * dt;
         double sr = 0, si = 0;
 #pragma unroll
         for (int q = 0; q < 14; ++q) {
             const double tau = t - rk[q] - td;
-            // tau^2 / (2 sigma^2), the product with the reciprocal corrected to a rounded quotient
-            const double a = tau * tau;
-            double e = a * i2;
-            e = fma(fma(-e, d2, a), i2, e);
-            const double gg = exp(-e);
-            const double dg = -(tau * (2.0 * i2)) * gg, wg = w * gg;
-            // (dg + j w gg) proj (c + j s)
-            sr += dg * pc[q] - wg * ps[q];
-            si += dg * ps[q] + wg * pc[q];
+            const double gg = exp(-quotient(tau * tau, d2, i2));
+            const double dg = -quotient(tau, s2, i1) * gg;
+            // (dg + j w gg) (c + j s)
+            sr += pr[q] * (dg * c[q] - w * gg * sn[q]);
+            si += pr[q] * (dg * sn[q] + w * gg * c[q]);
         }
         V[((size_t)l * nb + b) * ns + k] = zd{sr, si};
     }

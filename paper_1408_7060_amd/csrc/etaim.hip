@@ -52,6 +52,15 @@ constexpr size_t kMaxGridY = 65535;
 constexpr size_t kMaxBlocks256 = ((size_t)1 << 24) - 8;
 // batches up to this many columns apply the preconditioner with lane groups per row
 constexpr int kSpmvGroupMaxB = 4;
+// the anterpolation takes lane groups per (node, column) sum for up to two
+// columns and for up to this many sums: a group reads its node's entries for
+// one column, where the lane-per-column kernel shares them between columns
+// but needs enough sums to fill the card.  x stage, groups / lanes in us:
+// level-4 sphere FP32 26-29 / 33.0 at 1 column, 27.7 / 33.7 at 2, 38.1 / 35.6
+// at 4 (105 K sums), 55.6 / 44.4 at 8; level-5 sphere 87 / 104 at 2,
+// 154 / 143 at 4; level-3 sphere FP64 28.7 / 27.4 at 8 (60 K sums)
+constexpr int kAnterpGroupCols = 2;
+constexpr size_t kAnterpGroupMax = 32768;
 // most blocks one dot product or norm is split over
 constexpr int kRedMaxChunks = 64;
 
@@ -93,7 +102,7 @@ struct etaim_ctx {
     void *lamH_r = nullptr, *ghatH_r = nullptr, *ghatHT_r = nullptr, *farH = nullptr;
     int farH_slots = 0, farH_r0 = -1, pass = 0;
     // working-precision arrays (float or double)
-    void *lam_r = nullptr, *nw_r = nullptr, *near_r = nullptr, *nearT_r = nullptr, *ghat_r = nullptr, *tw_r[3] = {};
+    void *lam_r = nullptr, *nw_r = nullptr, *near_r = nullptr, *nearT_r = nullptr, *near0_r = nullptr, *nearT0_r = nullptr, *ghat_r = nullptr, *tw_r[3] = {};
     void* ghatT_r = nullptr;  // ky/kz-exchanged copy for the z-lines-first plane kernel
     void *A = nullptr, *P = nullptr, *ring = nullptr;
     void* S = nullptr;  // line-pass engine: full-spectrum work array [bc][kx][kz][ky] (allocated on first use)
@@ -557,7 +566,11 @@ struct Ops {
             if (!xs_ready)
                 hipLaunchKernelGGL(k_prescale<R>, dim3(blocks_for(nB)), dim3(256), 0, c->stream, x, dinv, xs, c->ns,
                                    c->B, conj_in, gate);
-            if (c->n_anodes > 0)
+            const size_t na = (size_t)c->n_anodes * c->B;
+            if (na > 0 && (c->B <= kAnterpGroupCols || na <= kAnterpGroupMax))
+                hipLaunchKernelGGL(k_anterp_grp<R>, dim3(blocks_for(na * kAnterpLanes)), dim3(256), 0, c->stream, xs,
+                                   c->anodes, c->n_anodes, c->nptr, c->nk, (const R*)c->nw_r, Q(c), g, c->B, gate);
+            else if (na > 0)
                 hipLaunchKernelGGL(k_anterp_nz<R>, dim3(blocks_for((size_t)c->n_anodes * c->B)), dim3(256), 0,
                                    c->stream, xs, c->anodes, c->n_anodes, c->nptr, c->nk, (const R*)c->nw_r, Q(c), g,
                                    c->B, gate);
@@ -672,6 +685,10 @@ struct Ops {
         if (mode == 0 && (c->x_engine != 1 || conj_x))
             hipLaunchKernelGGL(k_prescale<R>, dim3(blocks_for(nB)), dim3(256), 0, c->stream, x, dinv, xs, c->ns, c->B,
                                conj_x, gate);
+        // the product with Z_0 reads the near-zone values of m = 0 from their own array
+        const bool m0 = mode == 0 && m == 0;
+        const cplx<R>* nv = m0 ? (const cplx<R>*)(conj_v ? c->nearT0_r : c->near0_r) : nearv(c, conj_v);
+        const int mvv = m0 ? 1 : c->mv;
         if (c->interp_engine == 1 && c->ntiles > 0 && mode <= 1) {
             const int gc = interp_tile_gc<R>(c);
             const int nblk = c->ntiles * ((c->B + gc - 1) / gc);
@@ -679,7 +696,7 @@ struct Ops {
             const size_t lds = interp_tile_lds<R>(c);
 #define ETAIM_TILE(GC)                                                                                               \
     hipLaunchKernelGGL((k_interp_tile<R, GC>), tg, dim3(kTileThreads), lds, c->stream, (const cplx<R>*)P(c), (const R*)c->lam_r, \
-                       c->i0, c->tptr, c->tbase, c->torg, c->ntiles, c->gd, c->rowptr, c->col, nearv(c, conj_v), c->mv, \
+                       c->i0, c->tptr, c->tbase, c->torg, c->ntiles, c->gd, c->rowptr, c->col, nv, mvv, \
                        (const cplx<R>*)xs, m, (const cplx<R>*)c->hist, std::max(c->st.mn, 1), cur, nmh, V, y, c->ns,   \
                        mode, conj_v, gate, sr)
             switch (gc) {
@@ -691,10 +708,18 @@ struct Ops {
             HIPCHK(hipGetLastError());
             return ETAIM_OK;
         }
-        hipLaunchKernelGGL(k_interp_near<R>, grid, dim3(64 * wpb), 0, c->stream, (const cplx<R>*)P(c),
-                           (const R*)c->lam_r, c->i0, c->korder, c->gd, c->rowptr, c->col, nearv(c, conj_v), c->mv,
-                           (const cplx<R>*)xs, m, (const cplx<R>*)c->hist, std::max(c->st.mn, 1), cur, nmh, V, y,
-                           c->ns, mode, conj_v, gate, sr);
+#define ETAIM_INTERP(NC)                                                                                              \
+    hipLaunchKernelGGL((k_interp_near<R, NC>), grid, dim3(64 * wpb), 0, c->stream, (const cplx<R>*)P(c),              \
+                       (const R*)c->lam_r, c->i0, c->korder, c->gd, c->rowptr, c->col, nv, mvv,                       \
+                       (const cplx<R>*)xs, m, (const cplx<R>*)c->hist, std::max(c->st.mn, 1), cur, nmh, V, y, c->ns,  \
+                       mode, conj_v, gate, sr)
+        if (c->B == 1)
+            ETAIM_INTERP(1);
+        else if (c->B <= 4)
+            ETAIM_INTERP(4);
+        else
+            ETAIM_INTERP(32);
+#undef ETAIM_INTERP
         HIPCHK(hipGetLastError());
         return ETAIM_OK;
     }
@@ -2033,6 +2058,18 @@ int make_working(etaim_ctx* c) {
         c->nw_r = nw;
         c->near_r = nearv;
         c->ghat_r = gh;
+    }
+    {
+        // the values of Z_0 alone, for the products of the iteration
+        cplx<R>* v0 = nullptr;
+        CHK(c->alloc(v0, 2 * (size_t)c->nnz));
+        hipLaunchKernelGGL(k_take_column<R>, dim3(blocks_for((size_t)c->nnz)), dim3(256), 0, c->stream,
+                           (const cplx<R>*)c->near_r, v0, (size_t)c->nnz, c->mv);
+        hipLaunchKernelGGL(k_take_column<R>, dim3(blocks_for((size_t)c->nnz)), dim3(256), 0, c->stream,
+                           (const cplx<R>*)c->nearT_r, v0 + c->nnz, (size_t)c->nnz, c->mv);
+        HIPCHK(hipGetLastError());
+        c->near0_r = v0;
+        c->nearT0_r = v0 + c->nnz;
     }
     if (const int qn = quad_n(c)) {
         const size_t planes = (size_t)(c->st.ng + 1) * 2 * (c->gd.N[0] + 1), n1 = (size_t)qn + 1;

@@ -535,6 +535,13 @@ __global__ void k_permute_rows(const zd* __restrict__ in, zd* __restrict__ out, 
     }
 }
 
+// out[e] = in[e][0] (rows of mv values)
+template <typename R>
+__global__ void k_take_column(const cplx<R>* __restrict__ in, cplx<R>* __restrict__ out, size_t n, int mv) {
+    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x)
+        out[e] = in[e * mv];
+}
+
 template <typename R>
 __global__ void k_to_r(const zd* __restrict__ in, cplx<R>* __restrict__ out, size_t n) {
     for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x)
