@@ -1037,33 +1037,24 @@ struct Ops {
         return interp_near(c, mode, nullptr, nullptr, 0, cur, nmh, V, rhs, conj, 0, sr.live, sr);
     }
     // push the converged I_cur into the spectrum ring and the current ring
-    static int commit(etaim_ctx* c, int cur, const zd* x, StepRef sr = {}) {
-        const size_t slot_sz = (size_t)4 * c->B * c->Np;
-        if (sr.sd) {
-            // replayed: the commit kernel and the history store take the step from its descriptor
-            CHK(commit_slot(c, ring(c), x, sr));
-            if (c->st.mn >= 1) {
-                const size_t n = (size_t)c->B * c->ns;
-                hipLaunchKernelGGL(k_store_hist<R>, dim3(blocks_for(n)), dim3(256), 0, c->stream, x, (cplx<R>*)c->hist,
-                                   c->ns, c->B, c->st.mn, sr);
-                HIPCHK(hipGetLastError());
-            }
-            return ETAIM_OK;
-        }
-        CHK(commit_slot(c, ring(c) + (size_t)(cur % c->st.ng) * slot_sz, x));
-        if (c->st.mn >= 1) {
-            const size_t n = (size_t)c->B * c->ns;
-            // current history slot in the working precision, columns of a basis contiguous
-            hipLaunchKernelGGL(k_prescale<R>, dim3(blocks_for(n)), dim3(256), 0, c->stream, x, nullptr,
-                               (cplx<R>*)c->hist + (size_t)(cur % c->st.mn) * n, c->ns, c->B, 0, nullptr);
+    // (out: also store it there; replayed: into the call's I_out)
+    static int commit(etaim_ctx* c, int cur, const zd* x, zd* out = nullptr, StepRef sr = {}) {
+        const size_t n = (size_t)c->B * c->ns, slot_sz = (size_t)4 * c->B * c->Np;
+        const bool graph = sr.sd != nullptr, xs = c->x_engine == 1;
+        cplx<R>* hist = c->st.mn >= 1 ? (cplx<R>*)c->hist + (graph ? 0 : (size_t)(cur % c->st.mn) * n) : nullptr;
+        if (out || hist || graph) {
+            hipLaunchKernelGGL(k_store_step<R>, dim3(blocks_for(n)), dim3(256), 0, c->stream, x, out, hist,
+                               xs ? (cplx<R>*)c->xs : (cplx<R>*)nullptr, c->ns, c->B, std::max(c->st.mn, 1), sr);
             HIPCHK(hipGetLastError());
         }
-        return ETAIM_OK;
+        // replayed: the commit kernel takes the step from its descriptor
+        return commit_slot(c, graph ? ring(c) : ring(c) + (size_t)(cur % c->st.ng) * slot_sz, x, sr,
+                           xs && (out || hist || graph));
     }
     // anterpolate + forward FFT of the B columns of x into the spectrum slot
     // `slot` (replayed: the ring's base, the kernel picks the step's slot)
-    static int commit_slot(etaim_ctx* c, cplx<R>* slot, const zd* x, StepRef sr = {}) {
-        CHK(forward_x(c, x, nullptr, 0, sr.live));
+    static int commit_slot(etaim_ctx* c, cplx<R>* slot, const zd* x, StepRef sr = {}, bool xs_ready = false) {
+        CHK(forward_x(c, x, nullptr, 0, sr.live, xs_ready));
         if (sr.sd && c->yz_engine != 2)
             return fail(ETAIM_EUNSUPPORTED, "whole-step graph: needs the z-lines-first plane kernels");
         const GridDims& g = c->gd;
@@ -1140,14 +1131,26 @@ struct StepResult {
     double resid = 0;
 };
 
-// One Arnoldi step j for every active column: matvec, two classical
-// Gram-Schmidt passes, norm, scale, Givens update (flag[0] = columns still
-// active afterwards).  With a gate every kernel first checks the step's
-// live flag (k_gate), so steps can be enqueued ahead of the host's
-// convergence check or replayed from a captured graph.
+// one-launch orthogonalisation of step j: up to kOrthEntries basis entries per
+// column, with the column in one block's registers.  One compute unit reads
+// 32768 entries four times in about 22 us, the dot, update and tail launches
+// it replaces take 22 us (1920 entries, 17 vectors); the 4 m plate's 4961
+// entries took 21 us in one launch up to 6 vectors
+constexpr int kOrthEntries = 32768, kOrthMaxNs = 8 * kRedThreads, kOrthMaxJ = 128;
+inline bool orth_fused(int ns, int j) {
+    return ns <= kOrthMaxNs && j < kOrthMaxJ && (long long)(j + 1) * ns <= kOrthEntries;
+}
+// columns up to this length start a cycle in one block each (k_cycle_begin)
+constexpr int kCycleMaxNs = 8192;
 // blocks per dot product or norm: one per 16 K entries, at most 64
 inline int red_chunks(int ns) { return std::max(1, std::min(kRedMaxChunks, ns / 16384)); }
 
+// One Arnoldi step j for every active column: matvec, two classical
+// Gram-Schmidt passes, norm, scale, Givens update (flag[0] = columns still
+// active afterwards).  With a gate every kernel first checks the step's
+// live flag (set by the cycle start and the end of the step before), so
+// steps can be enqueued ahead of the host's convergence check or replayed
+// from a captured graph.
 template <typename R>
 int arnoldi_step(etaim_ctx* c, int j, int conj, const int* gate, const int* step_live = nullptr) {
     const int B = c->B, ns = c->ns, rs = c->prm.restart;
@@ -1155,7 +1158,6 @@ int arnoldi_step(etaim_ctx* c, int j, int conj, const int* gate, const int* step
     const zd* dinv = conj ? c->dinv_c : c->dinv;
     zd* vj = c->Vk + (size_t)j * nB;
     zd* vn = c->Vk + (size_t)(j + 1) * nB;
-    if (gate) hipLaunchKernelGGL(k_gate, dim3(1), dim3(64), 0, c->stream, c->flag, step_live);
     // few columns: lane groups per row (the column-lane kernels would leave
     // most lanes idle)
     const bool grp = B <= kSpmvGroupMaxB;
@@ -1194,8 +1196,27 @@ int arnoldi_step(etaim_ctx* c, int j, int conj, const int* gate, const int* step
     } else {
         CHK(Ops<R>::apply(c, 0, vj, dinv, c->w, conj, gate));
     }
-    dim3 gd(j + 1, B), go((ns + 255) / 256, B);
     Trace tk(c, ETAIM_K_KRYLOV, (4.0 * (j + 1) + 8.0) * (double)nB * 16.0);
+    if (orth_fused(ns, j)) {
+        // the whole orthogonalisation and update, one block per column
+        const size_t lds = ((size_t)(j + 1) * (kRedThreads / 64 + 2) + j + 2) * sizeof(zd) + (size_t)(j + 1) * sizeof(double);
+#define ETAIM_ORTH(S)                                                                                              \
+    hipLaunchKernelGGL(k_arnoldi_orth<S>, dim3(B), dim3(kRedThreads), lds, c->stream, c->Vk, c->w, c->H, c->cs, c->sn, \
+                       c->g, c->active, c->jcnt, c->resid, c->bnorm, c->flag, ns, j, B, rs, c->prm.tol, gate, step_live)
+        const int per = (ns + kRedThreads - 1) / kRedThreads;
+        if (per <= 1)
+            ETAIM_ORTH(1);
+        else if (per <= 2)
+            ETAIM_ORTH(2);
+        else if (per <= 4)
+            ETAIM_ORTH(4);
+        else
+            ETAIM_ORTH(8);
+#undef ETAIM_ORTH
+        HIPCHK(hipGetLastError());
+        return ETAIM_OK;
+    }
+    dim3 gd(j + 1, B), go((ns + 255) / 256, B);
     // long columns: each dot product and norm over several blocks, finished in order
     const int nch = red_chunks(ns);
     auto dots = [&](zd* h) {
@@ -1212,18 +1233,17 @@ int arnoldi_step(etaim_ctx* c, int j, int conj, const int* gate, const int* step
     hipLaunchKernelGGL(k_orth, go, dim3(256), 0, c->stream, c->Vk, c->w, c->h1, j + 1, ns, B, gate);
     dots(c->h2);
     hipLaunchKernelGGL(k_orth, go, dim3(256), 0, c->stream, c->Vk, c->w, c->h2, j + 1, ns, B, gate);
-    if (nch == 1) {
-        hipLaunchKernelGGL(k_norm, dim3(B), dim3(kRedThreads), 0, c->stream, c->w, c->nrm, ns, gate);
-    } else {
+    if (nch > 1) {
         hipLaunchKernelGGL(k_norm_part, dim3(B, nch), dim3(kRedThreads), 0, c->stream, c->w, (double*)c->redpart, ns,
                            nch, gate);
         hipLaunchKernelGGL(k_norm_fin, dim3((B + 63) / 64), dim3(64), 0, c->stream, (const double*)c->redpart, c->nrm,
                            B, nch, gate);
+        hipLaunchKernelGGL(k_scale, dim3(blocks_for(nB)), dim3(256), 0, c->stream, c->w, c->nrm, vn, ns, B, gate);
     }
-    hipLaunchKernelGGL(k_scale, dim3(blocks_for(nB)), dim3(256), 0, c->stream, c->w, c->nrm, vn, ns, B, gate);
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, c->stream, c->flag, 1, 0, gate);
-    hipLaunchKernelGGL(k_arnoldi_update, dim3(1), dim3(256), 0, c->stream, c->h1, c->h2, c->nrm, c->H, c->cs, c->sn,
-                       c->g, c->active, c->jcnt, c->resid, c->bnorm, c->flag, j, B, rs, c->prm.tol, gate);
+    const size_t lds = (size_t)(2 * j + 3) * sizeof(zd) + (size_t)(j + 1) * sizeof(double);
+    hipLaunchKernelGGL(k_arnoldi_tail, dim3(B), dim3(kRedThreads), lds, c->stream, c->w, vn, c->h1, c->h2,
+                       nch > 1 ? (const double*)c->nrm : (const double*)nullptr, c->H, c->cs, c->sn, c->g, c->active,
+                       c->jcnt, c->resid, c->bnorm, c->flag, ns, j, B, rs, c->prm.tol, gate, step_live);
     HIPCHK(hipGetLastError());
     return ETAIM_OK;
 }
@@ -1261,6 +1281,27 @@ int arnoldi_step_graph(etaim_ctx* c, int j, int conj) {
     return ETAIM_OK;
 }
 
+// Start of a GMRES cycle from w = A x: r = rhs - w, the norms (of rhs too in
+// the first cycle, short columns), the flags with `budget` steps and the
+// first basis vector.
+int cycle_begin(etaim_ctx* c, const zd* rhs, int budget, bool first, const int* gate) {
+    const int B = c->B, ns = c->ns;
+    const size_t nB = (size_t)B * ns;
+    if (ns <= kCycleMaxNs) {
+        hipLaunchKernelGGL(k_cycle_begin, dim3(B), dim3(kRedThreads), 0, c->stream, rhs, c->w, c->Vk, c->beta, c->bnorm,
+                           c->active, c->jcnt, c->g, c->resid, c->flag, ns, B, c->ldg, c->prm.tol, budget, first ? 1 : 0,
+                           gate);
+    } else {
+        hipLaunchKernelGGL(k_residual, dim3(blocks_for(nB)), dim3(256), 0, c->stream, rhs, c->w, nB, gate);
+        hipLaunchKernelGGL(k_norm, dim3(B), dim3(kRedThreads), 0, c->stream, c->w, c->beta, ns, gate, StepRef{});
+        hipLaunchKernelGGL(k_cycle_start, dim3(1), dim3(256), 0, c->stream, c->beta, c->bnorm, c->active, c->jcnt, c->g,
+                           c->resid, c->flag, B, c->ldg, c->prm.tol, budget, gate);
+        hipLaunchKernelGGL(k_scale, dim3(blocks_for(nB)), dim3(256), 0, c->stream, c->w, c->beta, c->Vk, ns, B, gate);
+    }
+    HIPCHK(hipGetLastError());
+    return ETAIM_OK;
+}
+
 // GMRES for one time step: x (in: initial guess, out: solution).
 // Every column b of the batch has its own Krylov space; columns leave the
 // iteration as they converge (device-side masks).
@@ -1275,19 +1316,15 @@ int gmres(etaim_ctx* c, const zd* rhs, zd* x, int conj, StepResult& res) {
     const bool graph = c->use_graph && !c->prof;
     const bool gated = graph || c->sync_every > 1;
     const int chunk = gated ? std::max(c->sync_every, 1) : 1;
-    hipLaunchKernelGGL(k_norm, dim3(B), dim3(kRedThreads), 0, c->stream, rhs, c->bnorm, ns, nullptr);
+    const bool begin1 = ns <= kCycleMaxNs;
+    if (!begin1)
+        hipLaunchKernelGGL(k_norm, dim3(B), dim3(kRedThreads), 0, c->stream, rhs, c->bnorm, ns, nullptr, StepRef{});
     int total = 0;
     double prev_worst = 0;
     for (int cycle = 0;; ++cycle) {
         // r = rhs - A x
         CHK(Ops<R>::apply(c, 0, x, nullptr, c->w, conj));
-        hipLaunchKernelGGL(k_residual, dim3(blocks_for(nB)), dim3(256), 0, c->stream, rhs, c->w, nB);
-        hipLaunchKernelGGL(k_norm, dim3(B), dim3(kRedThreads), 0, c->stream, c->w, c->beta, ns, nullptr);
-        hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, c->stream, c->flag, 4, 0, nullptr);
-        hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, c->stream, c->flag + 4, 1,
-                           std::max(c->prm.maxit - total, 0), nullptr);
-        hipLaunchKernelGGL(k_cycle_start, dim3(1), dim3(256), 0, c->stream, c->beta, c->bnorm, c->active, c->jcnt,
-                           c->g, c->resid, c->flag, B, c->ldg, tol);
+        CHK(cycle_begin(c, rhs, std::max(c->prm.maxit - total, 0), cycle == 0, nullptr));
         // the first cycle of a gated solve goes straight on to its Arnoldi steps:
         // the gate holds them back if no column is active, and the host reads the
         // cycle start's flags and residuals with the first chunk's
@@ -1318,8 +1355,6 @@ int gmres(etaim_ctx* c, const zd* rhs, zd* x, int conj, StepResult& res) {
             }
             prev_worst = worst;
         }
-        hipLaunchKernelGGL(k_scale, dim3(blocks_for(nB)), dim3(256), 0, c->stream, c->w, c->beta, c->Vk, ns, B,
-                           nullptr);
         const int base = total;
         // first chunk of a solve: as many steps as the previous solve took (the
         // count is steady along a march), so that no step is enqueued past
@@ -1356,8 +1391,7 @@ int gmres(etaim_ctx* c, const zd* rhs, zd* x, int conj, StepResult& res) {
             if (c->flag_h[1]) res.nonfinite = true;
             if (c->flag_h[0] == 0 || c->flag_h[1] || total >= c->prm.maxit) break;
         }
-        hipLaunchKernelGGL(k_backsolve, dim3((B + 63) / 64), dim3(64), 0, c->stream, c->H, c->g, c->jcnt, c->yv, B,
-                           rs);
+        hipLaunchKernelGGL(k_backsolve, dim3(B), dim3(64), 0, c->stream, c->H, c->g, c->jcnt, c->yv, rs, nullptr);
         if (c->precond == 1) {
             // x += M (V y): the combination, transposed to [ns][B] (in w, free
             // until the next cycle start), then the rows of M on the lanes' columns
@@ -1424,18 +1458,12 @@ int step_body(etaim_ctx* c, int J, int far, int pred) {
     hipLaunchKernelGGL(k_extrap, dim3(blocks_for(nB)), dim3(256), 0, c->stream, (const zd*)nullptr, c->xk, nB, 0LL, 1,
                        0, (const int*)c->pnext, sr);
     // GMRES, one cycle (the first cycle of the gated eager solve)
-    hipLaunchKernelGGL(k_norm, dim3(B), dim3(kRedThreads), 0, c->stream, c->rhs, c->bnorm, ns, live, StepRef{});
+    if (ns > kCycleMaxNs)
+        hipLaunchKernelGGL(k_norm, dim3(B), dim3(kRedThreads), 0, c->stream, c->rhs, c->bnorm, ns, live, StepRef{});
     CHK(Ops<R>::apply(c, 0, c->xk, nullptr, c->w, 0, live));
-    hipLaunchKernelGGL(k_residual, dim3(blocks_for(nB)), dim3(256), 0, c->stream, c->rhs, c->w, nB, live);
-    hipLaunchKernelGGL(k_norm, dim3(B), dim3(kRedThreads), 0, c->stream, c->w, c->beta, ns, live, StepRef{});
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, c->stream, c->flag, 4, 0, live);
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, c->stream, c->flag + 4, 1, c->prm.maxit, live);
-    hipLaunchKernelGGL(k_cycle_start, dim3(1), dim3(256), 0, c->stream, c->beta, c->bnorm, c->active, c->jcnt, c->g,
-                       c->resid, c->flag, B, c->ldg, c->prm.tol, live);
-    hipLaunchKernelGGL(k_scale, dim3(blocks_for(nB)), dim3(256), 0, c->stream, c->w, c->beta, c->Vk, ns, B, live);
+    CHK(cycle_begin(c, c->rhs, c->prm.maxit, true, live));
     for (int j = 0; j < J; ++j) CHK(arnoldi_step<R>(c, j, 0, c->flag + 2, live));
-    hipLaunchKernelGGL(k_backsolve, dim3((B + 63) / 64), dim3(64), 0, c->stream, c->H, c->g, c->jcnt, c->yv, B, rs,
-                       live);
+    hipLaunchKernelGGL(k_backsolve, dim3(B), dim3(64), 0, c->stream, c->H, c->g, c->jcnt, c->yv, rs, live);
     if (c->precond == 1) {
         hipLaunchKernelGGL(k_krylov_combine, dim3((ns + 255) / 256, B), dim3(256), 0, c->stream, c->zt, c->Vk, c->yv,
                            c->jcnt, ns, B, rs, live);
@@ -1456,8 +1484,7 @@ int step_body(etaim_ctx* c, int J, int far, int pred) {
     }
     hipLaunchKernelGGL(k_step_check, dim3(1), dim3(64), 0, c->stream, c->flag, c->sctl + 1);
     // the solution, the rings, the detector's norms, the next extrapolation order
-    hipLaunchKernelGGL(k_store_step, dim3(blocks_for(nB)), dim3(256), 0, c->stream, c->xk, nB, sr);
-    CHK(Ops<R>::commit(c, 0, c->xk, sr));
+    CHK(Ops<R>::commit(c, 0, c->xk, nullptr, sr));
     hipLaunchKernelGGL(k_norm, dim3(B), dim3(kRedThreads), 0, c->stream, c->xk, nullptr, ns, live, sr);
     if (pred) {
         hipLaunchKernelGGL(k_pred_err, dim3(kPredBlocks), dim3(kRedThreads), 0, c->stream, (const zd*)nullptr, nB, 0LL,
@@ -1771,12 +1798,11 @@ int march_impl(etaim_ctx* c, const zd* V, zd* I, etaim_stats* st, bool adjoint, 
             ev_step = -1;
         }
         HIPCHK(hipEventRecord(ev[2], c->stream));
-        HIPCHK(hipMemcpyAsync(Il, c->xk, nB * sizeof(zd), hipMemcpyDeviceToDevice, c->stream));
+        CHK(Ops<R>::commit(c, r, c->xk, Il));
         if (checking && nchk < chk_steps.size() && chk_steps[nchk] == r) {
             CHK(check_step<R>(c, r, Vl, I, Il, chk + 2 * (size_t)ccols * nchk));
             ++nchk;
         }
-        CHK(Ops<R>::commit(c, r, c->xk));
         hipLaunchKernelGGL(k_norm, dim3(B), dim3(kRedThreads), 0, c->stream, c->xk, nrm_all + (size_t)i * B, ns,
                            nullptr, StepRef{});
         const int pmax = std::min(r, c->guess_order);
@@ -2382,7 +2408,8 @@ int device_setup(etaim_ctx* c) {
     CHK(c->alloc(c->resid, c->B));
     CHK(c->alloc(c->active, c->B));
     CHK(c->alloc(c->jcnt, c->B));
-    CHK(c->alloc(c->flag, 8));
+    CHK(c->alloc(c->flag, kFlags));
+    HIPCHK(hipMemsetAsync(c->flag, 0, kFlags * sizeof(int), c->stream));
     CHK(c->alloc(c->perr, kMaxGuess + kMaxGuess * kPredBlocks));
     HIPCHK(hipHostMalloc((void**)&c->flag_h, 8 * sizeof(int), hipHostMallocDefault));
     HIPCHK(hipHostMalloc((void**)&c->res_h, 2 * (size_t)c->B * sizeof(double), hipHostMallocDefault));

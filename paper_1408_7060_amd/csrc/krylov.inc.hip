@@ -23,10 +23,38 @@ __device__ __forceinline__ double block_sum256(double v, double* sh) {
 // a reduction (one per column) keep enough loads in flight
 constexpr int kRedThreads = 1024;
 
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov(double v) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// sum over a wave by the butterfly over lane distances 32, 16, 8, 4, 2, 1,
+// with register moves between lanes (half and quarter swaps, rotations of
+// rows of 16, quad permutations) instead of LDS permutes
+__device__ __forceinline__ double wave_total(double v) {
+    {
+        const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+        v = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    }
+    {
+        const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+        v = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    }
+    v += dpp_mov<0x128>(v);  // row rotated by 8
+    v += dpp_mov<0x124>(v);  // by 4
+    v += dpp_mov<0x4e>(v);   // quad lanes 2 3 0 1
+    v += dpp_mov<0xb1>(v);   // 1 0 3 2
+    return v;
+}
+
 // deterministic sum over a kRedThreads block, valid in thread 0: a fixed
 // butterfly within each wave, then the wave sums in order
 __device__ __forceinline__ double block_sum_t0(double v, double* sh) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v = wave_total(v);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
     double r = 0;
@@ -159,120 +187,398 @@ __global__ void k_residual(const zd* __restrict__ rhs, zd* __restrict__ r, size_
         r[e] = rhs[e] - r[e];
 }
 
-// Start of a cycle: beta = ||r||; column active iff beta > tol * bnorm.
-// g[b] = (beta, 0, ...), jcnt = 0.  flag[0] = number of active columns,
-// flag[1] set on a non-finite residual.  One block, one thread per column
-// (strided); flag must be zero on entry.
+// The iteration's flags: {active columns, non-finite, the next Arnoldi step
+// is live, steps taken this cycle, step budget, -, column count (64 bits)}.
+// A step is live while a column is active, nothing went non-finite and the
+// budget lasts (and, in a whole-step graph, the step is).
+constexpr int kFlags = 8;
+
+// Counts a column done, with its state, in the flags' column count: the
+// columns in the low 24 bits, the active ones from bit 24, the non-finite
+// ones from bit 48, all in one atomic word, so that no fence is needed (a
+// device-wide fence writes back the L2).  True in the last of the B columns,
+// whose cnt and bad then hold the sums; the count is zero on entry and left
+// zero.
+__device__ __forceinline__ bool last_column(int* __restrict__ flag, int on, int bad_in, int B, int& cnt, int& bad) {
+    cnt = on;
+    bad = bad_in;
+    if (B == 1) return true;
+    unsigned long long* word = reinterpret_cast<unsigned long long*>(flag + 6);
+    const unsigned long long mine = 1ull | (unsigned long long)on << 24 | (unsigned long long)bad_in << 48;
+    const unsigned long long old = atomicAdd(word, mine), tot = old + mine;
+    if ((int)(tot & 0xffffff) != B) return false;
+    *word = 0;
+    cnt = (int)((tot >> 24) & 0xffffff);
+    bad = tot >> 48 ? 1 : 0;
+    return true;
+}
+
+// Start of a column's cycle: beta = ||r||; active iff beta > tol * bnorm.
+// g[b] = (beta, 0, ...), jcnt = 0.  Returns {active, finite}.
+__device__ __forceinline__ int2 start_column(double be, double bn, int* __restrict__ active, int* __restrict__ jcnt,
+                                             zd* __restrict__ g, double* __restrict__ resid, int b, int ldg,
+                                             double tol) {
+    const bool fin = isfinite(be);
+    const int a = (fin && be > tol * bn) ? 1 : 0;
+    active[b] = a;
+    jcnt[b] = 0;
+    resid[b] = bn > 0 ? be / bn : 0.0;
+    for (int i = 0; i < ldg; ++i) g[(size_t)b * ldg + i] = zd{0, 0};
+    g[(size_t)b * ldg] = zd{be, 0};
+    return int2{a, fin ? 1 : 0};
+}
+
+// Start of a cycle for every column, and its flags.  One block, one thread
+// per column (strided).
 __global__ void __launch_bounds__(256) k_cycle_start(const double* __restrict__ beta, const double* __restrict__ bnorm,
                                                      int* __restrict__ active, int* __restrict__ jcnt,
                                                      zd* __restrict__ g, double* __restrict__ resid,
-                                                     int* __restrict__ flag, int B, int ldg, double tol,
+                                                     int* __restrict__ flag, int B, int ldg, double tol, int budget,
                                                      const int* __restrict__ gate = nullptr) {
-    if (gated_off(gate)) return;
+    if (gated_off(gate)) {
+        if (threadIdx.x == 0) flag[2] = 0;
+        return;
+    }
+    __shared__ int cnt, bad;
+    if (threadIdx.x == 0) cnt = bad = 0;
+    __syncthreads();
     for (int b = threadIdx.x; b < B; b += blockDim.x) {
-        const double be = beta[b];
-        const bool fin = isfinite(be);
-        const int a = (fin && be > tol * bnorm[b]) ? 1 : 0;
-        active[b] = a;
-        jcnt[b] = 0;
-        resid[b] = bnorm[b] > 0 ? be / bnorm[b] : 0.0;
-        for (int i = 0; i < ldg; ++i) g[(size_t)b * ldg + i] = zd{0, 0};
-        g[(size_t)b * ldg] = zd{be, 0};
-        if (a) atomicAdd(&flag[0], 1);
-        if (!fin) atomicOr(&flag[1], 1);
+        const int2 r = start_column(beta[b], bnorm[b], active, jcnt, g, resid, b, ldg, tol);
+        if (r.x) atomicAdd(&cnt, 1);
+        if (!r.y) atomicOr(&bad, 1);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        flag[0] = cnt;
+        flag[1] = bad;
+        flag[2] = cnt > 0 && !bad && budget > 0 ? 1 : 0;
+        flag[3] = 0;
+        flag[4] = budget;
     }
 }
 
-// Arnoldi column j for each active column b: Hessenberg entries
-// h1 + h2 (the two classical Gram-Schmidt passes) and h_{j+1,j} = nrm[b],
-// previous Givens rotations, a new rotation, residual estimate |g_{j+1}|.
-// One block, one thread per column (strided); flag[0] must be zero on entry,
-// flag[1] (non-finite) is sticky until the next cycle start.
-__global__ void __launch_bounds__(256) k_arnoldi_update(const zd* __restrict__ h1, const zd* __restrict__ h2,
-                                                        const double* __restrict__ nrm, zd* __restrict__ H,
-                                                        double* __restrict__ cs, zd* __restrict__ sn,
-                                                        zd* __restrict__ g, int* __restrict__ active,
-                                                        int* __restrict__ jcnt, double* __restrict__ resid,
-                                                        const double* __restrict__ bnorm, int* __restrict__ flag,
-                                                        int j, int B, int restart, double tol,
-                                                        const int* __restrict__ gate) {
+// The same from the step's right-hand side and w = A x, for columns that one
+// block holds: r = rhs - w (stored in w), ||rhs||, ||r||, the cycle start and
+// the first basis vector r / ||r||, in one launch instead of seven of a few
+// microseconds each.  bnorm is formed where first != 0.  The column that
+// ends last sets the flags.
+__global__ void __launch_bounds__(kRedThreads) k_cycle_begin(const zd* __restrict__ rhs, zd* __restrict__ w,
+                                                             zd* __restrict__ V, double* __restrict__ beta,
+                                                             double* __restrict__ bnorm, int* __restrict__ active,
+                                                             int* __restrict__ jcnt, zd* __restrict__ g,
+                                                             double* __restrict__ resid, int* __restrict__ flag, int ns,
+                                                             int B, int ldg, double tol, int budget, int first,
+                                                             const int* __restrict__ gate = nullptr) {
+    if (gated_off(gate)) {
+        if (threadIdx.x == 0 && blockIdx.x == 0) flag[2] = 0;
+        return;
+    }
+    __shared__ double sh[2][kRedThreads / 64], be_s;
+    const int b = blockIdx.x;
+    const zd* rb = rhs + (size_t)b * ns;
+    zd* wb = w + (size_t)b * ns;
+    double sb = 0, sr = 0;
+    for (int k = threadIdx.x; k < ns; k += kRedThreads) {
+        const zd v = rb[k], r = v - wb[k];
+        wb[k] = r;
+        sb += v.x * v.x + v.y * v.y;
+        sr += r.x * r.x + r.y * r.y;
+    }
+    if (first) sb = block_sum_t0(sb, sh[0]);
+    sr = block_sum_t0(sr, sh[1]);
+    if (threadIdx.x == 0) be_s = sqrt(sr);
+    __syncthreads();
+    const double be = be_s, sc = be > 0 ? 1.0 / be : 0.0;
+    zd* vb = V + (size_t)b * ns;
+    for (int k = threadIdx.x; k < ns; k += kRedThreads) vb[k] = zd{wb[k].x * sc, wb[k].y * sc};
+    if (threadIdx.x != 0) return;
+    if (first) bnorm[b] = sqrt(sb);
+    beta[b] = be;
+    const int2 r = start_column(be, first ? sqrt(sb) : bnorm[b], active, jcnt, g, resid, b, ldg, tol);
+    int cnt, bad;
+    if (!last_column(flag, r.x, !r.y, B, cnt, bad)) return;
+    flag[0] = cnt;
+    flag[1] = bad;
+    flag[2] = cnt > 0 && !bad && budget > 0 ? 1 : 0;
+    flag[3] = 0;
+    flag[4] = budget;
+}
+
+// Arnoldi column j of column b, from its Hessenberg entries col[0..j] (the
+// two classical Gram-Schmidt passes added) and h_{j+1,j} = nrm: previous
+// Givens rotations c, s, a new rotation, residual estimate |g_{j+1}|.  One
+// thread; col[0..j+1], c and s are copies the block holds in LDS.  Returns
+// {active, finite}.
+__device__ __forceinline__ int2 givens_column(zd* col, double* c, zd* s, double nrm, zd* __restrict__ g,
+                                              int* __restrict__ active, int* __restrict__ jcnt,
+                                              double* __restrict__ resid, double bn, int j, int b, int restart,
+                                              double tol) {
+    zd a = col[0];
+    for (int i = 0; i < j; ++i) {
+        const zd bb = col[i + 1];
+        col[i] = c[i] * a + s[i] * bb;
+        a = c[i] * bb - conjz(s[i]) * a;
+    }
+    const double aa = sqrt(a.x * a.x + a.y * a.y);
+    const double r = sqrt(aa * aa + nrm * nrm);
+    double cj;
+    zd sj;
+    if (aa == 0.0) {
+        cj = 0.0;
+        sj = zd{1.0, 0.0};
+    } else {
+        cj = aa / r;
+        sj = zd{a.x / aa * nrm / r, a.y / aa * nrm / r};
+    }
+    c[j] = cj;
+    s[j] = sj;
+    col[j] = cj * a + sj * zd{nrm, 0};
+    col[j + 1] = zd{0, 0};
+    zd* gb = g + (size_t)b * (restart + 1);
+    const zd gj = gb[j];
+    gb[j] = cj * gj;
+    const zd gn = zd{0, 0} - conjz(sj) * gj;
+    gb[j + 1] = gn;
+    const double est = sqrt(gn.x * gn.x + gn.y * gn.y);
+    resid[b] = bn > 0 ? est / bn : 0.0;
+    jcnt[b] = j + 1;
+    const bool fin = isfinite(est);
+    const int on = fin && !(est <= tol * bn || nrm == 0.0 || j + 1 == restart) ? 1 : 0;
+    active[b] = on;
+    return int2{on, fin ? 1 : 0};
+}
+
+// A column's end of an Arnoldi step (one thread): the column that ends last
+// sets the flags and the next step's gate.  A non-finite column is sticky
+// until the next cycle start.
+__device__ __forceinline__ void step_done(int* __restrict__ flag, int on, int bad_in, int B, bool gated,
+                                          const int* __restrict__ step_live) {
+    int cnt, bad;
+    if (!last_column(flag, on, bad_in, B, cnt, bad)) return;
+    const int nf = flag[1] | bad;
+    flag[0] = cnt;
+    flag[1] = nf;
+    if (!gated) return;
+    const int left = flag[4] - 1;
+    flag[3] += 1;
+    flag[4] = left;
+    flag[2] = (cnt > 0 && nf == 0 && left > 0 && (step_live == nullptr || *step_live != 0)) ? 1 : 0;
+}
+
+// Last part of Arnoldi step j, one block per column: norm of w, the next
+// basis vector w / norm, Hessenberg column and Givens update, flags.  With
+// nrm given, the norm is formed and the vector scaled beforehand (columns
+// longer than a block should run over).
+__global__ void __launch_bounds__(kRedThreads) k_arnoldi_tail(const zd* __restrict__ w, zd* __restrict__ vn,
+                                                              const zd* __restrict__ h1, const zd* __restrict__ h2,
+                                                              const double* __restrict__ nrm, zd* __restrict__ H,
+                                                              double* __restrict__ cs, zd* __restrict__ sn,
+                                                              zd* __restrict__ g, int* __restrict__ active,
+                                                              int* __restrict__ jcnt, double* __restrict__ resid,
+                                                              const double* __restrict__ bnorm, int* __restrict__ flag,
+                                                              int ns, int j, int B, int restart, double tol,
+                                                              const int* __restrict__ gate,
+                                                              const int* __restrict__ step_live) {
     if (gated_off(gate)) return;
-    const int ldh = restart + 1;
-    for (int b = threadIdx.x; b < B; b += blockDim.x) {
-        if (!active[b]) continue;
-        zd* col = H + ((size_t)b * restart + j) * ldh;
-        for (int i = 0; i <= j; ++i) col[i] = h1[(size_t)i * B + b] + h2[(size_t)i * B + b];
-        col[j + 1] = zd{nrm[b], 0};
-        double* c = cs + (size_t)b * restart;
-        zd* s = sn + (size_t)b * restart;
-        for (int i = 0; i < j; ++i) {
-            const zd a = col[i], bb = col[i + 1];
-            col[i] = c[i] * a + s[i] * bb;
-            col[i + 1] = c[i] * bb - conjz(s[i]) * a;
+    extern __shared__ unsigned char smem_raw[];
+    zd* col = reinterpret_cast<zd*>(smem_raw);  // [j + 2]
+    zd* s = col + j + 2;                        // [j + 1]
+    double* c = reinterpret_cast<double*>(s + j + 1);  // [j + 1]
+    __shared__ double sh[kRedThreads / 64], n_s;
+    const int b = blockIdx.x, tid = threadIdx.x;
+    const int was = active[b];
+    int2 r{0, 1};
+    if (was) {
+        for (int i = tid; i <= j; i += kRedThreads) col[i] = h1[(size_t)i * B + b] + h2[(size_t)i * B + b];
+        for (int i = tid; i < j; i += kRedThreads) {
+            c[i] = cs[(size_t)b * restart + i];
+            s[i] = sn[(size_t)b * restart + i];
         }
-        const zd a = col[j];
-        const double bv = col[j + 1].x;
-        const double aa = sqrt(a.x * a.x + a.y * a.y);
-        const double r = sqrt(aa * aa + bv * bv);
-        double cj;
-        zd sj;
-        if (aa == 0.0) {
-            cj = 0.0;
-            sj = zd{1.0, 0.0};
+        if (nrm) {
+            if (tid == 0) n_s = nrm[b];
+            __syncthreads();
         } else {
-            cj = aa / r;
-            sj = zd{a.x / aa * bv / r, a.y / aa * bv / r};
+            const zd* x = w + (size_t)b * ns;
+            double t = 0;
+            for (int k = tid; k < ns; k += kRedThreads) t += x[k].x * x[k].x + x[k].y * x[k].y;
+            t = block_sum_t0(t, sh);
+            if (tid == 0) n_s = sqrt(t);
+            __syncthreads();
+            const double n = n_s, f = n > 0 ? 1.0 / n : 0.0;
+            zd* o = vn + (size_t)b * ns;
+            for (int k = tid; k < ns; k += kRedThreads) o[k] = zd{x[k].x * f, x[k].y * f};
         }
-        c[j] = cj;
-        s[j] = sj;
-        col[j] = cj * a + sj * col[j + 1];
-        col[j + 1] = zd{0, 0};
-        zd* gb = g + (size_t)b * ldh;
-        const zd gj = gb[j];
-        gb[j] = cj * gj;
-        gb[j + 1] = zd{0, 0} - conjz(sj) * gj;
-        const double est = sqrt(gb[j + 1].x * gb[j + 1].x + gb[j + 1].y * gb[j + 1].y);
-        resid[b] = bnorm[b] > 0 ? est / bnorm[b] : 0.0;
-        jcnt[b] = j + 1;
-        if (!isfinite(est)) {
-            atomicOr(&flag[1], 1);
-            active[b] = 0;
-        } else if (est <= tol * bnorm[b] || nrm[b] == 0.0 || j + 1 == restart) {
-            active[b] = 0;
+        if (tid == 0) {
+            r = givens_column(col, c, s, n_s, g, active, jcnt, resid, bnorm[b], j, b, restart, tol);
+            cs[(size_t)b * restart + j] = c[j];
+            sn[(size_t)b * restart + j] = s[j];
         }
-        if (active[b]) atomicAdd(&flag[0], 1);
+        __syncthreads();
+        zd* hc = H + ((size_t)b * restart + j) * (restart + 1);
+        for (int i = tid; i <= j + 1; i += kRedThreads) hc[i] = col[i];
     }
+    if (tid == 0) step_done(flag, r.x, !r.y, B, gate != nullptr, step_live);
 }
 
-// Gate of one Arnoldi step, flag = {active columns, non-finite, live,
-// steps taken this cycle, step budget}: the step is live while a column is
-// active, nothing went non-finite and the budget lasts.  One thread.
-__global__ void k_gate(int* __restrict__ flag, const int* __restrict__ step_live = nullptr) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const int live =
-        (flag[0] > 0 && flag[1] == 0 && flag[4] > 0 && (step_live == nullptr || *step_live != 0)) ? 1 : 0;
-    flag[2] = live;
-    if (live) {
-        flag[3] += 1;
-        flag[4] -= 1;
-    }
-}
-
-// Back-substitution R y = g per column (size jcnt[b]); y[b][i].
-__global__ void k_backsolve(const zd* __restrict__ H, const zd* __restrict__ g, const int* __restrict__ jcnt,
-                            zd* __restrict__ y, int B, int restart, const int* __restrict__ gate = nullptr) {
+// The whole orthogonalisation of Arnoldi step j in one launch, one block per
+// column: two classical Gram-Schmidt passes (h = V^H w, w -= V h), norm, next
+// basis vector, Hessenberg column and Givens update, flags.  A thread holds
+// S entries of w (k = thread + kRedThreads s); the sums run in the order of
+// k_dots, k_orth and k_norm, so the results are theirs bit for bit.  Bound by
+// one compute unit reading the basis four times; for short columns that is
+// less than the eight launches it replaces: 14 us against 24 for one column
+// of 480 entries (steps 0 to 24), 21 against 26 of 1920.
+template <int S>
+__global__ void __launch_bounds__(kRedThreads) k_arnoldi_orth(zd* __restrict__ V, const zd* __restrict__ w,
+                                                              zd* __restrict__ H, double* __restrict__ cs,
+                                                              zd* __restrict__ sn, zd* __restrict__ g,
+                                                              int* __restrict__ active, int* __restrict__ jcnt,
+                                                              double* __restrict__ resid,
+                                                              const double* __restrict__ bnorm, int* __restrict__ flag,
+                                                              int ns, int j, int B, int restart, double tol,
+                                                              const int* __restrict__ gate,
+                                                              const int* __restrict__ step_live) {
     if (gated_off(gate)) return;
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
+    constexpr int NW = kRedThreads / 64;
+    extern __shared__ unsigned char smem_raw[];
+    zd* red = reinterpret_cast<zd*>(smem_raw);  // [j + 1][NW]
+    zd* h = red + (j + 1) * NW;                 // [j + 1]
+    zd* col = h + j + 1;                        // [j + 2]
+    zd* s = col + j + 2;                        // [j + 1]
+    double* c = reinterpret_cast<double*>(s + j + 1);  // [j + 1]
+    __shared__ double sh[NW], n_s;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nv = j + 1;
+    int2 r{0, 1};
+    if (active[b]) {
+        const size_t step = (size_t)B * ns;
+        const zd* vb = V + (size_t)b * ns;
+        zd x[S];
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const int k = tid + kRedThreads * q;
+            x[q] = k < ns ? w[(size_t)b * ns + k] : zd{0, 0};
+        }
+        for (int i = tid; i < j; i += kRedThreads) {
+            c[i] = cs[(size_t)b * restart + i];
+            s[i] = sn[(size_t)b * restart + i];
+        }
+        // U basis vectors' entries at a time, their loads in flight together
+        // (entries past the column or the basis: zeros)
+        constexpr int U = S == 1 ? 8 : S == 2 ? 4 : 2;
+        auto load = [&](int i0, zd(&a)[U][S]) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int q = 0; q < S; ++q) {
+                    const int k = tid + kRedThreads * q;
+                    a[u][q] = i0 + u < nv && k < ns ? vb[(i0 + u) * step + k] : zd{0, 0};
+                }
+        };
+        for (int pass = 0; pass < 2; ++pass) {
+            // (waves past the column's end hold zeros)
+            if (wave * 64 < ns) {
+                for (int i0 = 0; i0 < nv; i0 += U) {
+                    zd a[U][S];
+                    load(i0, a);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        if (i0 + u >= nv) break;
+                        double re = 0, im = 0;
+#pragma unroll
+                        for (int q = 0; q < S; ++q) {
+                            if (tid + kRedThreads * q < ns) {
+                                re += a[u][q].x * x[q].x + a[u][q].y * x[q].y;
+                                im += a[u][q].x * x[q].y - a[u][q].y * x[q].x;
+                            }
+                        }
+                        re = wave_total(re);
+                        im = wave_total(im);
+                        if (lane == 0) red[(i0 + u) * NW + wave] = zd{re, im};
+                    }
+                }
+            } else if (lane == 0) {
+                for (int i = 0; i < nv; ++i) red[i * NW + wave] = zd{0, 0};
+            }
+            __syncthreads();
+            for (int i = tid; i < nv; i += kRedThreads) {
+                zd t{0, 0};
+                for (int q = 0; q < NW; ++q) t += red[i * NW + q];
+                h[i] = t;
+                col[i] = pass == 0 ? t : col[i] + t;
+            }
+            __syncthreads();
+            for (int i0 = 0; i0 < nv; i0 += U) {
+                zd a[U][S];
+                load(i0, a);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (i0 + u >= nv) break;
+                    const zd hi = h[i0 + u];
+#pragma unroll
+                    for (int q = 0; q < S; ++q) x[q] -= hi * a[u][q];
+                }
+            }
+        }
+        double t = 0;
+#pragma unroll
+        for (int q = 0; q < S; ++q)
+            if (tid + kRedThreads * q < ns) t += x[q].x * x[q].x + x[q].y * x[q].y;
+        t = block_sum_t0(t, sh);
+        if (tid == 0) n_s = sqrt(t);
+        __syncthreads();
+        const double n = n_s, f = n > 0 ? 1.0 / n : 0.0;
+        zd* o = V + (size_t)nv * step + (size_t)b * ns;
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const int k = tid + kRedThreads * q;
+            if (k < ns) o[k] = zd{x[q].x * f, x[q].y * f};
+        }
+        if (tid == 0) {
+            r = givens_column(col, c, s, n, g, active, jcnt, resid, bnorm[b], j, b, restart, tol);
+            cs[(size_t)b * restart + j] = c[j];
+            sn[(size_t)b * restart + j] = s[j];
+        }
+        __syncthreads();
+        zd* hc = H + ((size_t)b * restart + j) * (restart + 1);
+        for (int i = tid; i <= j + 1; i += kRedThreads) hc[i] = col[i];
+    }
+    if (tid == 0) step_done(flag, r.x, !r.y, B, gate != nullptr, step_live);
+}
+
+// Back-substitution R y = g per column (size jcnt[b]); y[b][i].  One wave per
+// column: R (up to kBackLds columns) and g come to LDS first, so that the
+// serial chain of the sums waits on LDS and not on memory (one thread per
+// column on global memory: 21 us at 19 columns of R, this kernel 17).
+constexpr int kBackLds = 64;
+__global__ void __launch_bounds__(64) k_backsolve(const zd* __restrict__ H, const zd* __restrict__ g,
+                                                  const int* __restrict__ jcnt, zd* __restrict__ y, int restart,
+                                                  const int* __restrict__ gate = nullptr) {
+    if (gated_off(gate)) return;
+    __shared__ zd R[kBackLds * (kBackLds + 1) / 2], gs[kBackLds], ys[kBackLds];
+    const int b = blockIdx.x, tid = threadIdx.x;
     const int ldh = restart + 1;
     const int n = jcnt[b];
     zd* yb = y + (size_t)b * restart;
+    const zd* Hb = H + (size_t)b * restart * ldh;
+    const bool lds = n <= kBackLds;
+    if (lds) {
+        for (int q = 0; q < n; ++q)
+            if (tid <= q) R[q * (q + 1) / 2 + tid] = Hb[(size_t)q * ldh + tid];
+        if (tid < n) gs[tid] = g[(size_t)b * ldh + tid];
+    }
+    __syncthreads();
+    if (tid != 0) return;
     for (int i = n - 1; i >= 0; --i) {
-        zd acc = g[(size_t)b * ldh + i];
-        for (int q = i + 1; q < n; ++q) acc -= H[((size_t)b * restart + q) * ldh + i] * yb[q];
-        const zd d = H[((size_t)b * restart + i) * ldh + i];
+        zd acc = lds ? gs[i] : g[(size_t)b * ldh + i];
+        if (lds)
+            for (int q = i + 1; q < n; ++q) acc -= R[q * (q + 1) / 2 + i] * ys[q];
+        else
+            for (int q = i + 1; q < n; ++q) acc -= Hb[(size_t)q * ldh + i] * yb[q];
+        const zd d = lds ? R[i * (i + 1) / 2 + i] : Hb[(size_t)i * ldh + i];
         const double dd = d.x * d.x + d.y * d.y;
-        yb[i] = dd > 0 ? zd{(acc.x * d.x + acc.y * d.y) / dd, (acc.y * d.x - acc.x * d.y) / dd} : zd{0, 0};
+        const zd v = dd > 0 ? zd{(acc.x * d.x + acc.y * d.y) / dd, (acc.y * d.x - acc.x * d.y) / dd} : zd{0, 0};
+        yb[i] = v;
+        if (lds) ys[i] = v;
     }
 }
 
@@ -482,9 +788,15 @@ __global__ void __launch_bounds__(kRedThreads) k_pred_err(const zd* __restrict__
     for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < nB; e += (size_t)gridDim.x * blockDim.x) {
         const zd x = I[(size_t)l * nB + e];
         zd v[kMaxGuess];
-        for (int i = 1; i <= pmax; ++i) v[i - 1] = I[(size_t)(l - (long long)dir * i) * nB + e];
-        for (int p = 1; p <= pmax; ++p) {
+        // (fixed trip counts: the solutions stay in registers)
+#pragma unroll
+        for (int i = 1; i <= kMaxGuess; ++i)
+            v[i - 1] = i <= pmax ? I[(size_t)(l - (long long)dir * i) * nB + e] : zd{0, 0};
+#pragma unroll
+        for (int p = 1; p <= kMaxGuess; ++p) {
+            if (p > pmax) continue;
             double rx = x.x, ry = x.y;
+#pragma unroll
             for (int i = 1; i <= p; ++i) {
                 rx -= a[p - 1][i - 1] * v[i - 1].x;
                 ry -= a[p - 1][i - 1] * v[i - 1].y;
@@ -520,11 +832,6 @@ __global__ void __launch_bounds__(256) k_pred_err_sum(const double* __restrict__
     }
 }
 
-__global__ void k_fill_int(int* __restrict__ p, int n, int v, const int* __restrict__ gate = nullptr) {
-    if (gated_off(gate)) return;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = v;
-}
-
 // out[e][m] = in[perm[e]][m] (rows of mv values)
 __global__ void k_permute_rows(const zd* __restrict__ in, zd* __restrict__ out, const int* __restrict__ perm, int n,
                                int mv) {
@@ -548,28 +855,28 @@ __global__ void k_to_r(const zd* __restrict__ in, cplx<R>* __restrict__ out, siz
         out[e] = cplx<R>{(R)in[e].x, (R)in[e].y};
 }
 
-// The replayed step's solution x into the call's I_out[cur] ([N_t][B][ns]).
-__global__ void k_store_step(const zd* __restrict__ x, size_t nB, StepRef sr) {
-    if (step_off(sr)) return;
-    const StepDesc* d = step_of(sr);
-    zd* out = d->I + (size_t)d->cur * nB;
-    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < nB; e += (size_t)gridDim.x * blockDim.x)
-        out[e] = x[e];
-}
-
-// The replayed step's solution into its slot of the current history
-// [M_n][ns][B] in the working precision (columns of a basis contiguous).
+// A step's solution x into I_out (out, or the call's I_out[cur] of a replayed
+// step), and, in the working precision with the columns of a basis
+// contiguous, into its slot of the current history (slot, or the ring of mn
+// slots) and the scaled columns xs of the commit's anterpolation.  out, hist
+// and xs may be null.
 template <typename R>
-__global__ void k_store_hist(const zd* __restrict__ x, cplx<R>* __restrict__ hist, int ns, int B, int mn,
-                             StepRef sr) {
+__global__ void k_store_step(const zd* __restrict__ x, zd* __restrict__ out, cplx<R>* __restrict__ hist,
+                             cplx<R>* __restrict__ xs, int ns, int B, int mn, StepRef sr) {
     if (step_off(sr)) return;
-    const StepDesc* d = step_of(sr);
-    cplx<R>* out = hist + (size_t)(d->cur % mn) * ns * B;
     const size_t tot = (size_t)ns * B;
+    if (const StepDesc* d = step_of(sr)) {
+        out = d->I + (size_t)d->cur * tot;
+        if (hist) hist += (size_t)(d->cur % mn) * tot;
+    }
     for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < tot; e += (size_t)gridDim.x * blockDim.x) {
         const int k = (int)(e / B), b = (int)(e - (size_t)k * B);
-        const zd v = x[(size_t)b * ns + k];
-        out[e] = cplx<R>{(R)v.x, (R)v.y};
+        const size_t o = (size_t)b * ns + k;
+        const zd v = x[o];
+        const cplx<R> r{(R)v.x, (R)v.y};
+        if (out) out[o] = v;
+        if (hist) hist[e] = r;
+        if (xs) xs[e] = r;
     }
 }
 
