@@ -245,7 +245,7 @@ __global__ void __launch_bounds__(256) k_xfwd(const cplx<R>* __restrict__ q, cpl
     for (int x = 0; x < N; ++x) u[x] = *(((mk >> x) & 1ull) ? src + (size_t)x * Ny : zsrc);
     if (p) {
 #pragma unroll
-        for (int x = 1; x < N; ++x) u[x] = tw96_mul<R>(u[x], (96 / (2 * N)) * x, false);
+        for (int x = 1; x < N; ++x) u[x] = twn_mul<R, 2 * N>(u[x], x, false);
     }
     dft_small<R, N>(u, false);
     cplx<R>* dst = A + (size_t)bc * 2 * N * nl + (size_t)p * nl + line;
@@ -271,7 +271,7 @@ __global__ void __launch_bounds__(256) k_xinv(const cplx<R>* __restrict__ A, cpl
     dft_small<R, N>(u, true);
     if (p) {
 #pragma unroll
-        for (int x = 1; x < N; ++x) u[x] = tw96_mul<R>(u[x], (96 / (2 * N)) * x, true);
+        for (int x = 1; x < N; ++x) u[x] = twn_mul<R, 2 * N>(u[x], x, true);
     }
     const int z = line / Ny, y = line - z * Ny;
     cplx<R>* dst = P + (size_t)bc * N * nl + (size_t)z * N * Ny + y;
@@ -282,6 +282,11 @@ __global__ void __launch_bounds__(256) k_xinv(const cplx<R>* __restrict__ A, cpl
         const cplx<R> keep = p ? u[H + j] : u[j], send = p ? u[j] : u[H + j];
         const cplx<R> got{__shfl_xor(send.x, 1, 64), __shfl_xor(send.y, 1, 64)};
         dst[(size_t)(p * H + j) * Ny] = keep + got;
+    }
+    if constexpr (N % 2 == 1) {
+        // the last point of an odd line: lane 0 stores it
+        const cplx<R> got{__shfl_xor(u[N - 1].x, 1, 64), __shfl_xor(u[N - 1].y, 1, 64)};
+        if (!p) dst[(size_t)(N - 1) * Ny] = u[N - 1] + got;
     }
 }
 
@@ -746,15 +751,16 @@ k_yzc_commit(const cplx<R>* __restrict__ A, cplx<R>* __restrict__ slot, const cp
     }
 }
 
-// GT[p][a][b] = G[p][b][a] for the n x n planes p of a folded Green table
+// GT[p][ky][kz] = G[p][kz][ky] for the nz x ny planes p of a folded Green table
 template <typename R>
-__global__ void k_green_transpose(const cplx<R>* __restrict__ G, cplx<R>* __restrict__ GT, size_t planes, int n) {
-    const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    const size_t nn = (size_t)n * n;
-    if (i >= planes * nn) return;
-    const size_t p = i / nn;
-    const int r = (int)(i - p * nn), a = r / n, b = r - a * n;
-    GT[i] = G[p * nn + (size_t)b * n + a];
+__global__ void k_green_transpose(const cplx<R>* __restrict__ G, cplx<R>* __restrict__ GT, size_t planes, int ny,
+                                  int nz) {
+    const size_t nn = (size_t)ny * nz, tot = planes * nn;
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < tot; i += (size_t)gridDim.x * blockDim.x) {
+        const size_t p = i / nn;
+        const int r = (int)(i - p * nn), y = r / nz, z = r - y * nz;
+        GT[i] = G[p * nn + (size_t)z * ny + y];
+    }
 }
 
 // Commit y/z stage on the register path: forward transforms of the plane

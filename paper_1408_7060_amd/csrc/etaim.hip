@@ -19,6 +19,7 @@
 #include "context.hpp"
 #include "farfield.inc.hip"
 #include "krylov.inc.hip"
+#include "plane.inc.hip"
 
 using namespace etaim;
 
@@ -373,8 +374,10 @@ int launch_l4(etaim_ctx* c, bool lf, dim3 grid, const cplx<R>* in, cplx<R>* out,
     return lf ? launch_l4<R, A, B, true, false>(c, grid, in, out, tw, a)
               : launch_l4<R, A, B, false, false>(c, grid, in, out, tw, a);
 }
+// the register x-line instances of xline_n
+#define ETAIM_XLINES(X) X(16) X(18) X(24) X(27) X(32) X(36) X(48)
 // the four-step instances of lines4_split
-#define ETAIM_L4_SPLITS(X) X(8, 12) X(12, 12) X(8, 24) X(12, 24) X(16, 24) X(24, 24)
+#define ETAIM_L4_SPLITS(X) X(8, 12) X(6, 18) X(8, 16) X(12, 12) X(8, 24) X(12, 24) X(16, 24) X(24, 24)
 
 template <typename R>
 int launch_lines(etaim_ctx* c, const cplx<R>* in, cplx<R>* out, const cplx<R>* tw, const Radix& pl, int nf,
@@ -415,18 +418,29 @@ int launch_lines(etaim_ctx* c, const cplx<R>* in, cplx<R>* out, const cplx<R>* t
     return ETAIM_OK;
 }
 
-// N of the register x-line kernels (N_x = N, N | 48 with a register codelet), 0 if none
+// N of the register x-line kernels (N_x = N with a register codelet), 0 if none
 int xline_n(const etaim_ctx* c) {
     const int n = c->gd.N[0];
     if (c->gd.L[0] != 2 * n) return 0;
-    return (n == 16 || n == 24 || n == 48) ? n : 0;
+    return (n == 16 || n == 18 || n == 24 || n == 27 || n == 32 || n == 36 || n == 48) ? n : 0;
 }
 
-// the register x stage applies: a register x-line codelet, or four-step
-// lines of length L_x (the anterpolated grid is then transformed by them)
+// x_engine 1 can be set: N_x in {16, 24, 48}, or four-step lines of length
+// L_x = 2 N_x (the anterpolated grid is then transformed by them)
 bool xreg_ok(const etaim_ctx* c) {
+    const int n = c->gd.N[0];
+    if (n == 16 || n == 24 || n == 48) return true;
     int A = 0, B = 0;
-    return xline_n(c) > 0 || (c->gd.L[0] == 2 * c->gd.N[0] && lines4_split(c->gd.L[0], A, B));
+    return n != 54 && n != 64 && lines4_split(c->gd.L[0], A, B);
+}
+
+// x_engine 0 takes the register x stage as well where it has lines for this
+// grid (18, 27, 32, 36 as register codelets, 54 and 64 as four-step lines):
+// the LDS-staged lines with the gather fused in took 54 + 19 us for 5 columns
+// of an 18^3 grid in FP64 (level-3 sphere), the register stage 15 + 5 us
+bool xreg(const etaim_ctx* c) {
+    const int n = c->gd.N[0];
+    return c->x_engine == 1 || n == 18 || n == 27 || n == 32 || n == 36 || n == 54 || n == 64;
 }
 
 // N of the register quadrant kernels for this grid (N_y = N_z = N, N | 48
@@ -436,6 +450,23 @@ int quad_n(const etaim_ctx* c) {
     if (c->gd.N[2] != n || c->gd.L[1] != 2 * n || c->gd.L[2] != 2 * n) return 0;
     return (n == 16 || n == 24 || n == 48) ? n : 0;
 }
+
+// the y/z stage of the matvec by k_plane_green: the engines without register
+// plane kernels for this plane (0, LDS plane passes; 3, line passes through a
+// full-spectrum work array)
+bool plane_kernel(const etaim_ctx* c) {
+    if ((c->yz_engine != 0 && c->yz_engine != 3) || quad_n(c)) return false;
+    const int ny = c->gd.N[1], nz = c->gd.N[2];
+#define ETAIM_PLANE_HAS(NY, PY, NZ, PZ) if (ny == NY && nz == NZ) return true;
+    ETAIM_PLANES(ETAIM_PLANE_HAS)
+    if (c->prec == ETAIM_FP32) {
+        ETAIM_PLANES32(ETAIM_PLANE_HAS)
+    }
+#undef ETAIM_PLANE_HAS
+    return false;
+}
+// the Green table with ky and kz exchanged is needed
+bool green_t(const etaim_ctx* c) { return quad_n(c) > 0 || plane_kernel(c); }
 
 // columns per block of the grid-tile interpolation (a power of two, its LDS
 // box of 4 GC potential planes within 69 KB)
@@ -561,7 +592,7 @@ struct Ops {
         const double a_sz = 4.0 * c->B * g.L[0] * g.N[2] * g.N[1] * s;
         Trace t(c, ETAIM_K_ANTERP_X, nB * 16 + 64.0 * c->ns * (4 + 4 * sizeof(R)) + (c->N3 + 1) * 4.0 + a_sz +
                                          (dinv ? c->ns * 16.0 : 0.0));
-        if (c->x_engine == 1) {
+        if (xreg(c)) {
             cplx<R>* xs = (cplx<R>*)c->xs;
             if (!xs_ready)
                 hipLaunchKernelGGL(k_prescale<R>, dim3(blocks_for(nB)), dim3(256), 0, c->stream, x, dinv, xs, c->ns,
@@ -584,10 +615,11 @@ struct Ops {
             const dim3 gx((2 * g.N[1] * g.N[2] + 255) / 256, 4 * c->B);
             const cplx<R>* zsrc = (const cplx<R>*)c->zero;
             switch (xline_n(c)) {
-                case 16: hipLaunchKernelGGL((k_xfwd<R, 16>), gx, dim3(256), 0, c->stream, Q(c), A(c), g, c->xmask, zsrc, gate); break;
-                case 24: hipLaunchKernelGGL((k_xfwd<R, 24>), gx, dim3(256), 0, c->stream, Q(c), A(c), g, c->xmask, zsrc, gate); break;
-                case 48: hipLaunchKernelGGL((k_xfwd<R, 48>), gx, dim3(256), 0, c->stream, Q(c), A(c), g, c->xmask, zsrc, gate); break;
-                default: return fail(ETAIM_EUNSUPPORTED, "register x-line kernels need N_x in {16, 24, 48}");
+#define ETAIM_XFWD(N) \
+    case N: hipLaunchKernelGGL((k_xfwd<R, N>), gx, dim3(256), 0, c->stream, Q(c), A(c), g, c->xmask, zsrc, gate); break;
+                ETAIM_XLINES(ETAIM_XFWD)
+#undef ETAIM_XFWD
+                default: return fail(ETAIM_EUNSUPPORTED, "no register x-line kernel for this N_x");
             }
             HIPCHK(hipGetLastError());
             return ETAIM_OK;
@@ -603,14 +635,15 @@ struct Ops {
         const long long Lx = g.L[0], Nx = g.N[0], Ny = g.N[1], Nz = g.N[2];
         const double s = sizeof(cplx<R>), bc = 4.0 * c->B;
         // one register kernel (events on its dispatch) or the line launches
-        Trace t(c, ETAIM_K_FFT_X_INV, bc * Lx * Nz * Ny * s + bc * c->N3 * s, c->x_engine == 1 && xline_n(c) > 0);
-        if (c->x_engine == 1 && xline_n(c)) {
+        Trace t(c, ETAIM_K_FFT_X_INV, bc * Lx * Nz * Ny * s + bc * c->N3 * s, xreg(c) && xline_n(c) > 0);
+        if (xreg(c) && xline_n(c)) {
             const dim3 gx((unsigned)((2 * Ny * Nz + 255) / 256), (unsigned)(4 * c->B));
             switch (xline_n(c)) {
-                case 16: launch_timed(t, k_xinv<R, 16>, gx, dim3(256), 0, c->stream, A(c), P(c), g, gate); break;
-                case 24: launch_timed(t, k_xinv<R, 24>, gx, dim3(256), 0, c->stream, A(c), P(c), g, gate); break;
-                case 48: launch_timed(t, k_xinv<R, 48>, gx, dim3(256), 0, c->stream, A(c), P(c), g, gate); break;
-                default: return fail(ETAIM_EUNSUPPORTED, "register x-line kernels need N_x in {16, 24, 48}");
+#define ETAIM_XINV(N) \
+    case N: launch_timed(t, k_xinv<R, N>, gx, dim3(256), 0, c->stream, A(c), P(c), g, gate); break;
+                ETAIM_XLINES(ETAIM_XINV)
+#undef ETAIM_XINV
+                default: return fail(ETAIM_EUNSUPPORTED, "no register x-line kernel for this N_x");
             }
             HIPCHK(hipGetLastError());
             return ETAIM_OK;
@@ -625,10 +658,31 @@ struct Ops {
     }
     static size_t quad_lds(etaim_ctx* c) { return (size_t)4 * quad_n(c) * (quad_n(c) + 1) * sizeof(cplx<R>); }
     static size_t zline_lds(etaim_ctx* c) { return (size_t)2 * quad_n(c) * (quad_n(c) + 1) * sizeof(cplx<R>); }
+    // the plane kernel's instance for this (N_y, N_z)
+    static int plane_green(etaim_ctx* c, int m, int conj, const int* gate) {
+        const GridDims& g = c->gd;
+        const double s = sizeof(cplx<R>);
+        Trace t(c, ETAIM_K_YZ_GREEN, 2.0 * 4 * c->B * g.L[0] * g.N[2] * g.N[1] * s + 2.0 * c->gfold * s, true);
+        const cplx<R>* G = ghatT(c) + (size_t)m * 2 * c->gfold;
+#define ETAIM_PLANE_GREEN(NY, PY, NZ, PZ)                                                                              \
+    if (g.N[1] == NY && g.N[2] == NZ) {                                                                                \
+        launch_timed(t, k_plane_green<R, NY, PY, NZ, PZ>, dim3(4 * c->B, g.L[0]), dim3(plane_threads<R, NY, PY, NZ, PZ>()),       \
+                     plane_lds_bytes<R, NY, PY, NZ>(), c->stream, A(c), G, tw(c, 1), tw(c, 2), g, conj, gate);         \
+        HIPCHK(hipGetLastError());                                                                                     \
+        return ETAIM_OK;                                                                                               \
+    }
+        ETAIM_PLANES(ETAIM_PLANE_GREEN)
+        if constexpr (sizeof(R) == 4) {
+            ETAIM_PLANES32(ETAIM_PLANE_GREEN)
+        }
+#undef ETAIM_PLANE_GREEN
+        return fail(ETAIM_EUNSUPPORTED, "no plane kernel for this N_y, N_z");
+    }
     static int yz_green(etaim_ctx* c, int m, int conj, const int* gate = nullptr) {
         const GridDims& g = c->gd;
         dim3 grid(g.L[0], 4 * c->B);
         const double s = sizeof(cplx<R>);
+        if (plane_kernel(c)) return plane_green(c, m, conj, gate);
         if (c->yz_engine == 3) {
             CHK(ensure_S(c));
             Trace t(c, ETAIM_K_YZ_GREEN, 2.0 * 4 * c->B * g.L[0] * g.N[2] * g.N[1] * s + 2.0 * c->gfold * s);
@@ -682,7 +736,7 @@ struct Ops {
         cplx<R>* xs = (cplx<R>*)c->xs;
         // the near zone reads the scaled columns [ns][B]; the register x stage
         // has already written them for this x
-        if (mode == 0 && (c->x_engine != 1 || conj_x))
+        if (mode == 0 && (!xreg(c) || conj_x))
             hipLaunchKernelGGL(k_prescale<R>, dim3(blocks_for(nB)), dim3(256), 0, c->stream, x, dinv, xs, c->ns, c->B,
                                conj_x, gate);
         // the product with Z_0 reads the near-zone values of m = 0 from their own array
@@ -736,7 +790,7 @@ struct Ops {
         // the MFIE far part, added to y (the register x stage's scaled
         // columns are in place after the first pass)
         PassSwap ps(c);
-        CHK(forward_x(c, x, dinv, 0, gate, xs_ready || c->x_engine == 1));
+        CHK(forward_x(c, x, dinv, 0, gate, xs_ready || xreg(c)));
         CHK(yz_green(c, m, conj, gate));
         CHK(inverse_x(c, gate));
         return interp_near(c, 2, x, dinv, m, 0, 0, nullptr, y, conj, 0, gate);
@@ -1040,7 +1094,7 @@ struct Ops {
     // (out: also store it there; replayed: into the call's I_out)
     static int commit(etaim_ctx* c, int cur, const zd* x, zd* out = nullptr, StepRef sr = {}) {
         const size_t n = (size_t)c->B * c->ns, slot_sz = (size_t)4 * c->B * c->Np;
-        const bool graph = sr.sd != nullptr, xs = c->x_engine == 1;
+        const bool graph = sr.sd != nullptr, xs = xreg(c);
         cplx<R>* hist = c->st.mn >= 1 ? (cplx<R>*)c->hist + (graph ? 0 : (size_t)(cur % c->st.mn) * n) : nullptr;
         if (out || hist || graph) {
             hipLaunchKernelGGL(k_store_step<R>, dim3(blocks_for(n)), dim3(256), 0, c->stream, x, out, hist,
@@ -1113,6 +1167,15 @@ struct Ops {
             HIPCHK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
         HIPCHK(hipFuncSetAttribute((const void*)k_zlines_green<R>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                    160 * 1024));
+#define ETAIM_PLANE_LDS(NY, PY, NZ, PZ)                                                                      \
+    if (c->gd.N[1] == NY && c->gd.N[2] == NZ && plane_lds_bytes<R, NY, PY, NZ>() > 64 * 1024)                                                          \
+        HIPCHK(hipFuncSetAttribute((const void*)k_plane_green<R, NY, PY, NZ, PZ>,                              \
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+        ETAIM_PLANES(ETAIM_PLANE_LDS)
+        if constexpr (sizeof(R) == 4) {
+            ETAIM_PLANES32(ETAIM_PLANE_LDS)
+        }
+#undef ETAIM_PLANE_LDS
         for (const void* f : {(const void*)k_interp_tile<R, 1>, (const void*)k_interp_tile<R, 2>,
                               (const void*)k_interp_tile<R, 4>})
             HIPCHK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
@@ -1162,7 +1225,7 @@ int arnoldi_step(etaim_ctx* c, int j, int conj, const int* gate, const int* step
     // most lanes idle)
     const bool grp = B <= kSpmvGroupMaxB;
     const unsigned gblocks = (unsigned)((nB * kSpmvLanes + 255) / 256);
-    if (c->precond == 1 && c->x_engine == 1) {
+    if (c->precond == 1 && xreg(c)) {
         // w = Z (M v_j), M the near-zone sparse approximate inverse (M^H for the
         // adjoint): v_j transposed to [ns][B], then M v_j straight into the
         // operator's scaled-column buffer
@@ -2097,22 +2160,25 @@ int make_working(etaim_ctx* c) {
         c->near0_r = v0;
         c->nearT0_r = v0 + c->nnz;
     }
-    if (const int qn = quad_n(c)) {
-        const size_t planes = (size_t)(c->st.ng + 1) * 2 * (c->gd.N[0] + 1), n1 = (size_t)qn + 1;
-        cplx<R>* gt = nullptr;
-        CHK(c->alloc(gt, planes * n1 * n1));
-        hipLaunchKernelGGL(k_green_transpose<R>, dim3(blocks_for(planes * n1 * n1)), dim3(256), 0, c->stream,
-                           (const cplx<R>*)c->ghat_r, gt, planes, (int)n1);
-        HIPCHK(hipGetLastError());
-        c->ghatT_r = gt;
-        if (c->st.cfie) {
-            cplx<R>* gth = nullptr;
-            CHK(c->alloc(gth, planes * n1 * n1));
-            hipLaunchKernelGGL(k_green_transpose<R>, dim3(blocks_for(planes * n1 * n1)), dim3(256), 0, c->stream,
-                               (const cplx<R>*)c->ghatH_r, gth, planes, (int)n1);
+    // plane kernels: LDS and per-thread register staging limits; where the
+    // padded (y, z) plane does not fit, the line-pass engine takes the y/z stage
+    const bool plane_ok = Ops<R>::plane_lds(c) <= 160 * 1024 && plane_fits(c->gd.N[2], c->ry) &&
+                          plane_fits(c->gd.L[1], c->rz);
+    if (c->yz_engine == 0 && !plane_ok) c->yz_engine = 3;
+    if (green_t(c)) {
+        const size_t planes = (size_t)(c->st.ng + 1) * 2 * (c->gd.N[0] + 1);
+        const int ny = c->gd.N[1] + 1, nz = c->gd.N[2] + 1;
+        auto transposed = [&](const void* src, void*& dst) -> int {
+            cplx<R>* gt = nullptr;
+            CHK(c->alloc(gt, planes * ny * nz));
+            hipLaunchKernelGGL(k_green_transpose<R>, dim3(blocks_for(planes * ny * nz)), dim3(256), 0, c->stream,
+                               (const cplx<R>*)src, gt, planes, ny, nz);
             HIPCHK(hipGetLastError());
-            c->ghatHT_r = gth;
-        }
+            dst = gt;
+            return ETAIM_OK;
+        };
+        CHK(transposed(c->ghat_r, c->ghatT_r));
+        if (c->st.cfie) CHK(transposed(c->ghatH_r, c->ghatHT_r));
     }
     for (int a = 0; a < 3; ++a) {
         const int L = c->gd.L[a];
@@ -2127,18 +2193,13 @@ int make_working(etaim_ctx* c) {
     }
     CHK(c->allocv(c->A, 4 * nB * (size_t)c->gd.N[2] * c->gd.N[1] * c->gd.L[0] * sizeof(cplx<R>)));
     CHK(c->allocv(c->P, 4 * nB * c->N3 * sizeof(cplx<R>)));
-    if (xreg_ok(c)) {
+    if (xreg_ok(c) || xreg(c)) {
         CHK(c->allocv(c->Q, 4 * nB * c->N3 * sizeof(cplx<R>)));
         HIPCHK(hipMemsetAsync(c->Q, 0, 4 * nB * c->N3 * sizeof(cplx<R>), c->stream));
     }
     CHK(c->allocv(c->xs, nB * (size_t)c->ns * sizeof(cplx<R>)));
     const size_t ring_cols = c->ring_cols > 0 ? (size_t)c->ring_cols : nB;
     CHK(c->allocv(c->ring, (size_t)c->st.ng * 4 * ring_cols * c->Np * sizeof(cplx<R>)));
-    // plane kernels: LDS and per-thread register staging limits; where the
-    // padded (y, z) plane does not fit, the line-pass engine takes the y/z stage
-    const bool plane_ok = Ops<R>::plane_lds(c) <= 160 * 1024 && plane_fits(c->gd.N[2], c->ry) &&
-                          plane_fits(c->gd.L[1], c->rz);
-    if (c->yz_engine == 0 && !plane_ok) c->yz_engine = 3;
     if (Ops<R>::gather_lds(c) > 160 * 1024 || !plane_fits(4, c->rx) ||
         (c->yz_engine == 3 && !(line_fits<R>(c->ry) && line_fits<R>(c->rz))))
         return fail(ETAIM_EUNSUPPORTED, "the padded grid's lines do not fit the LDS line kernels");

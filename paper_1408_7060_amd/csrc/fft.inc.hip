@@ -163,6 +163,63 @@ __device__ __forceinline__ cplx<R> tw96_mul(cplx<R> v, int m, bool inverse) {
     return cmul_fma(v, cplx<R>{(R)c, (R)s});
 }
 
+// exp(-2 pi i m / N), m < N, for codelet sizes that do not divide 48 (or 96):
+// cosines and sines by their Taylor series on [0, pi/4] (to 1 ulp), the rest
+// by symmetry, evaluated at compile time
+template <int N>
+struct Roots {
+    double c[N], s[N];
+};
+template <int N>
+__host__ __device__ constexpr Roots<N> make_roots() {
+    Roots<N> r{};
+    for (int m = 0; m < N; ++m) {
+        // angle 2 pi m / N as an octant o and the remainder e / (8 N) turns, e < N
+        const int o = 8 * m / N, e = 8 * m - o * N;
+        // within an odd octant, from its upper end
+        const int f = o % 2 ? N - e : e;
+        const double x = 2.0 * kPi * (double)f / (8.0 * (double)N), x2 = x * x;
+        double ct = 1.0, st = 1.0;
+        for (int k = 11; k >= 1; --k) {
+            ct = 1.0 - ct * x2 / (double)((2 * k - 1) * (2 * k));
+            st = 1.0 - st * x2 / (double)((2 * k) * (2 * k + 1));
+        }
+        st *= x;
+        double a = 0, b = 0;  // cos, sin of the angle
+        switch (o) {
+            case 0: a = ct; b = st; break;
+            case 1: a = st; b = ct; break;
+            case 2: a = -st; b = ct; break;
+            case 3: a = -ct; b = st; break;
+            case 4: a = -ct; b = -st; break;
+            case 5: a = -st; b = -ct; break;
+            case 6: a = st; b = -ct; break;
+            default: a = ct; b = -st; break;
+        }
+        r.c[m] = a;
+        r.s[m] = -b;
+    }
+    return r;
+}
+
+// v * exp(-+2 pi i m / N) for a compile-time m: exact swaps and negations at
+// multiples of 90 degrees, sqrt(1/2) (a +- b) at odd multiples of 45 degrees
+template <typename R, int N>
+__device__ __forceinline__ cplx<R> twn_mul(cplx<R> v, int m, bool inverse) {
+    if constexpr (48 % N == 0) {
+        return tw48_mul<R>(v, (48 / N) * m, inverse);
+    } else if constexpr (96 % N == 0) {
+        return tw96_mul<R>(v, (96 / N) * m, inverse);
+    } else {
+        constexpr Roots<N> t = make_roots<N>();
+        m %= N;
+        if (inverse) m = (N - m) % N;
+        if (N % 8 == 0 && 8 * m % N == 0) return tw48_mul<R>(v, 6 * (8 * m / N), false);
+        if (4 * m % N == 0) return tw48_mul<R>(v, 12 * (4 * m / N), false);
+        return cmul_fma(v, cplx<R>{(R)t.c[m], (R)t.s[m]});
+    }
+}
+
 // composite codelet of size N1*N2 in registers: X[k2 + N2 k1] =
 // sum_n1 W_N1^{n1 k1} W_N^{n1 k2} sum_n2 W_N2^{n2 k2} x[n1 + N1 n2]
 template <typename R, int N1, int N2>
@@ -177,7 +234,7 @@ __device__ __forceinline__ void dft_composite(cplx<R> (&u)[N1 * N2], bool invers
         dft_small<R, N2>(v, inverse);
 #pragma unroll
         for (int k2 = 0; k2 < N2; ++k2) {
-            y[n1][k2] = tw48_mul<R>(v[k2], (48 / N) * n1 * k2, inverse);
+            y[n1][k2] = twn_mul<R, N>(v[k2], n1 * k2, inverse);
         }
     }
 #pragma unroll
@@ -217,8 +274,18 @@ __device__ __forceinline__ void dft_small(cplx<R> (&u)[RAD], bool inverse) {
         dft_composite<R, 2, 3>(u, inverse);
     } else if constexpr (RAD == 8) {
         dft_composite<R, 2, 4>(u, inverse);
+    } else if constexpr (RAD == 9) {
+        dft_composite<R, 3, 3>(u, inverse);
     } else if constexpr (RAD == 12) {
         dft_composite<R, 4, 3>(u, inverse);
+    } else if constexpr (RAD == 18) {
+        dft_composite<R, 6, 3>(u, inverse);
+    } else if constexpr (RAD == 27) {
+        dft_composite<R, 9, 3>(u, inverse);
+    } else if constexpr (RAD == 32) {
+        dft_composite<R, 8, 4>(u, inverse);
+    } else if constexpr (RAD == 36) {
+        dft_composite<R, 12, 3>(u, inverse);
     } else if constexpr (RAD == 24) {
         dft_composite<R, 8, 3>(u, inverse);
     } else if constexpr (RAD == 48) {
@@ -567,6 +634,8 @@ __global__ void __launch_bounds__((lines4_threads<R, A, B>())) k_lines4(const cp
 inline bool lines4_split(int L, int& A, int& B) {
     switch (L) {
         case 96: A = 8; B = 12; return true;
+        case 108: A = 6; B = 18; return true;
+        case 128: A = 8; B = 16; return true;
         case 144: A = 12; B = 12; return true;
         case 192: A = 8; B = 24; return true;
         case 288: A = 12; B = 24; return true;
