@@ -32,17 +32,19 @@ template <typename R, int NY, int PY, int NZ>
 __host__ __device__ constexpr size_t plane_tile() {
     return (size_t)NZ * plane_ld(NY, PY) * sizeof(cplx<R>);
 }
-// both parities' tiles at once where they fit the LDS: with two blocks on a
-// CU, each thread takes its column for one pz after the other; else (half)
-// the threads double and each half takes one pz, so that the one block holds
-// as many waves and no partial result waits in registers
+// both parities' tiles at once where they fit the LDS: the threads double and
+// each half takes one pz (half), so that a block holds twice the waves and
+// no partial result waits in registers.  On flat planes, whose rows occupy a
+// wave either way, each thread takes its column for one pz after the other
+// (48x8 in FP64: 50 us for 8 columns, 59 with halves; the cubes 10 to 30 %
+// faster with halves at one column, equal at eight)
 template <typename R, int NY, int PY, int NZ>
 __host__ __device__ constexpr int plane_tz() {
     return 2 * plane_tile<R, NY, PY, NZ>() <= 156 * 1024 ? 2 : 1;
 }
 template <typename R, int NY, int PY, int NZ>
 __host__ __device__ constexpr bool plane_half() {
-    return plane_tz<R, NY, PY, NZ>() == 2 && 2 * plane_tile<R, NY, PY, NZ>() > 72 * 1024;
+    return plane_tz<R, NY, PY, NZ>() == 2 && (NZ > 8 || 2 * plane_tile<R, NY, PY, NZ>() > 72 * 1024);
 }
 // threads: a lane for every (column, p) of the z lines, whole waves
 template <typename R, int NY, int PY, int NZ, int PZ>
@@ -172,6 +174,13 @@ __attribute__((amdgpu_waves_per_eu(plane_waves<R, NY, PY, NZ, PZ>()))) k_plane_g
     cplx<R> acc[QZ];
 #pragma unroll
     for (int j = 0; j < QZ; ++j) acc[j] = cplx<R>{0, 0};
+    // short lines: read once and kept for the other parity
+    constexpr bool KEEP = QZ <= 12 && !HALF;
+    cplx<R> in[KEEP ? QZ : 1];
+    if constexpr (KEEP) {
+#pragma unroll
+        for (int j = 0; j < QZ; ++j) in[j] = zlive ? pl[(zp + PZ * j) * NY + y] : cplx<R>{0, 0};
+    }
     __syncthreads();
     for (int pz0 = 0; pz0 < 2; pz0 += TZ) {
 #pragma unroll 1
@@ -179,7 +188,7 @@ __attribute__((amdgpu_waves_per_eu(plane_waves<R, NY, PY, NZ, PZ>()))) k_plane_g
             const int pz = TZ == 2 ? t : pz0;
             cplx<R> u[QZ];
 #pragma unroll
-            for (int j = 0; j < QZ; ++j) u[j] = zlive ? pl[(zp + PZ * j) * NY + y] : cplx<R>{0, 0};
+            for (int j = 0; j < QZ; ++j) u[j] = KEEP ? in[KEEP ? j : 0] : zlive ? pl[(zp + PZ * j) * NY + y] : cplx<R>{0, 0};
             cplx<R>* col = tile + (size_t)t * NZ * LD + y;
             mline_fwd<R, PZ, QZ>(u, zp, pz, col, LD, twz + (pz * PZ + (zlive ? zp : 0)) * QZ, zlive);
             if (zlive) {
@@ -201,25 +210,31 @@ __attribute__((amdgpu_waves_per_eu(plane_waves<R, NY, PY, NZ, PZ>()))) k_plane_g
             const unsigned up = (unsigned)(2 * p * (NZ + 1) + zf), down = (unsigned)(2 * (PY - 1 - p) * (NZ + 1) + zf);
             // row x times w_{2N}^{py y}: DFT, Green product, inverse DFT, post-twiddle
             auto pass = [&](cplx<R>(&x)[QY], int py) {
+                // ky = 2 c + py of c = c0 + p: a group of PY lanes lies on one side of
+                // the fold at c = N_y / 2 (PY divides it), so that its address is a
+                // uniform row plus the lane's offset up or down
+                auto green = [&](int c0) -> cplx<R> {
+                    if constexpr (NY % (2 * PY) != 0)
+                        return Gk[fold(2 * (c0 + p) + py, 2 * NY) * (NZ + 1) + zf];
+                    else if (2 * c0 < NY)
+                        return (Gk + (2 * c0 + py) * (NZ + 1))[up];
+                    else
+                        return (Gk + (2 * NY - 2 * (c0 + PY - 1) - py) * (NZ + 1))[down];
+                };
+                // short lines: the Green values wait in registers
+                constexpr bool AHEAD = QY <= 12;
+                cplx<R> gr[AHEAD ? QY : 1];
+                if constexpr (AHEAD) {
+#pragma unroll
+                    for (int i = 0; i < QY; ++i) gr[i] = green(PY * (i / PY) + QY * (i % PY));
+                }
                 mline_fwd<R, PY, QY>(x, p, py, rp, 1, twy + (py * PY + p) * QY, live);
 #pragma unroll
-                for (int i = 0; i < QY / PY; ++i)
-#pragma unroll
-                    for (int q = 0; q < PY; ++q) {
-                        // ky = 2 c + py of c = c0 + p: a group of PY lanes lies on one side of
-                        // the fold at c = N_y / 2 (PY divides it), so that its address is a
-                        // uniform row plus the lane's offset up or down
-                        const int c0 = PY * i + QY * q;
-                        cplx<R> gv;
-                        if constexpr (NY % (2 * PY) != 0)
-                            gv = Gk[fold(2 * (c0 + p) + py, 2 * NY) * (NZ + 1) + zf];
-                        else if (2 * c0 < NY)
-                            gv = (Gk + (2 * c0 + py) * (NZ + 1))[up];
-                        else
-                            gv = (Gk + (2 * NY - 2 * (c0 + PY - 1) - py) * (NZ + 1))[down];
-                        if (conj_g) gv.y = -gv.y;
-                        x[i * PY + q] = cmul_fma(x[i * PY + q], gv);
-                    }
+                for (int i = 0; i < QY; ++i) {
+                    cplx<R> gv = AHEAD ? gr[AHEAD ? i : 0] : green(PY * (i / PY) + QY * (i % PY));
+                    if (conj_g) gv.y = -gv.y;
+                    x[i] = cmul_fma(x[i], gv);
+                }
                 mline_inv<R, PY, QY>(x, p, py, rp, 1, twy + (py * PY + p) * QY, live);
             };
             // py = 1 on a copy of the row (its LDS is the exchange's space),
