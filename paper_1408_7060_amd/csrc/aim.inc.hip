@@ -1245,7 +1245,8 @@ __global__ void __launch_bounds__(256) k_ring_far(const cplx<R>* __restrict__ ri
         constexpr int CH = 8;
 #pragma unroll
         for (int hp0 = 1; hp0 <= NGX; hp0 += CH) {
-            if (hp0 > ng) break;
+            // (steps before 0 are not read)
+            if (hp0 > ng || hp0 > r0) break;
             cplx<R> q[CH][P];
 #pragma unroll
             for (int u = 0; u < CH; ++u) {
@@ -1328,7 +1329,8 @@ __global__ void __launch_bounds__(256) k_ring_far3(const cplx<R>* __restrict__ r
         constexpr int CH = 8;
 #pragma unroll
         for (int hp0 = 1; hp0 <= NGX; hp0 += CH) {
-            if (hp0 > ng) break;
+            // (steps before 0 are not read)
+            if (hp0 > ng || hp0 > r0) break;
             cplx<R> t[CH][P];
 #pragma unroll
             for (int u = 0; u < CH; ++u) {
