@@ -51,6 +51,54 @@ __device__ __forceinline__ double wave_total(double v) {
     return v;
 }
 
+// The sums over a wave of NV values (a power of two up to 16), each by the
+// same butterfly as wave_total: at the first log2(NV) distances a lane pair
+// exchanges one value for another and each keeps half of them, so that all
+// NV take little more than twice one value's work.  Lane l then holds the
+// sum of value l / (64 / NV).
+// the value of lane l ^ 4: rows rotated left by 4 in the quads that need the
+// next one, right by 4 in the others
+__device__ __forceinline__ double lane_xor4(double v) {
+    int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x12c, 0xf, 0x5, false);
+    int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x12c, 0xf, 0x5, false);
+    lo = __builtin_amdgcn_update_dpp(lo, __double2loint(v), 0x124, 0xf, 0xa, false);
+    hi = __builtin_amdgcn_update_dpp(hi, __double2hiint(v), 0x124, 0xf, 0xa, false);
+    return __hiloint2double(hi, lo);
+}
+template <int NV>
+__device__ __forceinline__ double wave_totals(double (&t)[NV], int lane) {
+    auto swap32 = [](double a, double b) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+        return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    };
+    auto swap16 = [](double a, double b) {
+        const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+        return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    };
+    constexpr int H1 = NV / 2, H2 = NV / 4, H3 = NV / 8, H4 = NV / 16;
+    // (a value swapped with itself: the plain butterfly step)
+#pragma unroll
+    for (int i = 0; i < (H1 ? H1 : 1); ++i) t[i] = swap32(t[i], t[H1 ? i + H1 : i]);
+#pragma unroll
+    for (int i = 0; i < (H2 ? H2 : 1); ++i) t[i] = swap16(t[i], t[H2 ? i + H2 : i]);
+#pragma unroll
+    for (int i = 0; i < (H3 ? H3 : 1); ++i) {
+        const bool up = H3 && (lane & 8) != 0;
+        const double o = t[H3 ? i + H3 : i];
+        t[i] = (up ? o : t[i]) + dpp_mov<0x128>(up ? t[i] : o);
+    }
+    {
+        const bool up = H4 && (lane & 4) != 0;
+        const double o = t[H4 ? 1 : 0];
+        t[0] = (up ? o : t[0]) + lane_xor4(up ? t[0] : o);
+    }
+    t[0] += dpp_mov<0x4e>(t[0]);
+    t[0] += dpp_mov<0xb1>(t[0]);
+    return t[0];
+}
+
 // deterministic sum over a kRedThreads block, valid in thread 0: a fixed
 // butterfly within each wave, then the wave sums in order
 __device__ __forceinline__ double block_sum_t0(double v, double* sh) {
@@ -464,7 +512,7 @@ __global__ void __launch_bounds__(kRedThreads) k_arnoldi_orth(zd* __restrict__ V
         }
         // U basis vectors' entries at a time, their loads in flight together
         // (entries past the column or the basis: zeros)
-        constexpr int U = S == 1 ? 8 : S == 2 ? 4 : 2;
+        constexpr int U = S <= 2 ? 8 : S == 4 ? 4 : 2;
         auto load = [&](int i0, zd(&a)[U][S]) {
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -480,9 +528,9 @@ __global__ void __launch_bounds__(kRedThreads) k_arnoldi_orth(zd* __restrict__ V
                 for (int i0 = 0; i0 < nv; i0 += U) {
                     zd a[U][S];
                     load(i0, a);
+                    double t[2 * U];
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        if (i0 + u >= nv) break;
                         double re = 0, im = 0;
 #pragma unroll
                         for (int q = 0; q < S; ++q) {
@@ -491,10 +539,14 @@ __global__ void __launch_bounds__(kRedThreads) k_arnoldi_orth(zd* __restrict__ V
                                 im += a[u][q].x * x[q].y - a[u][q].y * x[q].x;
                             }
                         }
-                        re = wave_total(re);
-                        im = wave_total(im);
-                        if (lane == 0) red[(i0 + u) * NW + wave] = zd{re, im};
+                        t[2 * u] = re;
+                        t[2 * u + 1] = im;
                     }
+                    const double sum = wave_totals<2 * U>(t, lane);
+                    constexpr int GL = 64 / (2 * U);
+                    const int v = lane / GL;
+                    if (lane % GL == 0 && i0 + v / 2 < nv)
+                        reinterpret_cast<double*>(red + (i0 + v / 2) * NW + wave)[v & 1] = sum;
                 }
             } else if (lane == 0) {
                 for (int i = 0; i < nv; ++i) red[i * NW + wave] = zd{0, 0};
