@@ -1195,10 +1195,9 @@ struct StepResult {
 };
 
 // one-launch orthogonalisation of step j: up to kOrthEntries basis entries per
-// column, with the column in one block's registers.  One compute unit reads
-// 32768 entries four times in about 22 us, the dot, update and tail launches
-// it replaces take 22 us (1920 entries, 17 vectors); the 4 m plate's 4961
-// entries took 21 us in one launch up to 6 vectors
+// column, with the column in one block's registers.  One compute unit takes
+// about 22 us for 32768 entries (1920 entries, 17 vectors; 4961 entries, 6
+// vectors: 20 us), the dot, update and tail launches it replaces 22 us
 constexpr int kOrthEntries = 32768, kOrthMaxNs = 8 * kRedThreads, kOrthMaxJ = 128;
 inline bool orth_fused(int ns, int j) {
     return ns <= kOrthMaxNs && j < kOrthMaxJ && (long long)(j + 1) * ns <= kOrthEntries;

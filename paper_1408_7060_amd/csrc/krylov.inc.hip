@@ -474,8 +474,9 @@ __global__ void __launch_bounds__(kRedThreads) k_arnoldi_tail(const zd* __restri
 // S entries of w (k = thread + kRedThreads s); the sums run in the order of
 // k_dots, k_orth and k_norm, so the results are theirs bit for bit.  Bound by
 // one compute unit reading the basis four times; for short columns that is
-// less than the eight launches it replaces: 14 us against 24 for one column
-// of 480 entries (steps 0 to 24), 21 against 26 of 1920.
+// less than the eight launches it replaces: 11 us against 24 for one column
+// of 480 entries (steps 0 to 24), 17 against 26 of 1920 (steps 0 to 16); with
+// the first vectors read again for each use 12 and 20.
 template <int S>
 __global__ void __launch_bounds__(kRedThreads) k_arnoldi_orth(zd* __restrict__ V, const zd* __restrict__ w,
                                                               zd* __restrict__ H, double* __restrict__ cs,
@@ -512,7 +513,10 @@ __global__ void __launch_bounds__(kRedThreads) k_arnoldi_orth(zd* __restrict__ V
         }
         // U basis vectors' entries at a time, their loads in flight together
         // (entries past the column or the basis: zeros)
-        constexpr int U = S <= 2 ? 8 : S == 4 ? 4 : 2;
+        constexpr int U = S == 1 ? 8 : S <= 4 ? 4 : 2;
+        // (columns of up to two entries per thread: the first U vectors stay in
+        // registers for all four uses)
+        constexpr bool KEEP = S <= 2;
         auto load = [&](int i0, zd(&a)[U][S]) {
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -522,31 +526,37 @@ __global__ void __launch_bounds__(kRedThreads) k_arnoldi_orth(zd* __restrict__ V
                     a[u][q] = i0 + u < nv && k < ns ? vb[(i0 + u) * step + k] : zd{0, 0};
                 }
         };
+        zd first[KEEP ? U : 1][S];
+        if constexpr (KEEP) load(0, first);
         for (int pass = 0; pass < 2; ++pass) {
+            auto dots = [&](int i0, const zd(&a)[U][S]) {
+                double t[2 * U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    double re = 0, im = 0;
+#pragma unroll
+                    for (int q = 0; q < S; ++q) {
+                        if (tid + kRedThreads * q < ns) {
+                            re += a[u][q].x * x[q].x + a[u][q].y * x[q].y;
+                            im += a[u][q].x * x[q].y - a[u][q].y * x[q].x;
+                        }
+                    }
+                    t[2 * u] = re;
+                    t[2 * u + 1] = im;
+                }
+                const double sum = wave_totals<2 * U>(t, lane);
+                constexpr int GL = 64 / (2 * U);
+                const int v = lane / GL;
+                if (lane % GL == 0 && i0 + v / 2 < nv)
+                    reinterpret_cast<double*>(red + (i0 + v / 2) * NW + wave)[v & 1] = sum;
+            };
             // (waves past the column's end hold zeros)
             if (wave * 64 < ns) {
-                for (int i0 = 0; i0 < nv; i0 += U) {
+                if constexpr (KEEP) dots(0, first);
+                for (int i0 = KEEP ? U : 0; i0 < nv; i0 += U) {
                     zd a[U][S];
                     load(i0, a);
-                    double t[2 * U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        double re = 0, im = 0;
-#pragma unroll
-                        for (int q = 0; q < S; ++q) {
-                            if (tid + kRedThreads * q < ns) {
-                                re += a[u][q].x * x[q].x + a[u][q].y * x[q].y;
-                                im += a[u][q].x * x[q].y - a[u][q].y * x[q].x;
-                            }
-                        }
-                        t[2 * u] = re;
-                        t[2 * u + 1] = im;
-                    }
-                    const double sum = wave_totals<2 * U>(t, lane);
-                    constexpr int GL = 64 / (2 * U);
-                    const int v = lane / GL;
-                    if (lane % GL == 0 && i0 + v / 2 < nv)
-                        reinterpret_cast<double*>(red + (i0 + v / 2) * NW + wave)[v & 1] = sum;
+                    dots(i0, a);
                 }
             } else if (lane == 0) {
                 for (int i = 0; i < nv; ++i) red[i * NW + wave] = zd{0, 0};
@@ -559,9 +569,7 @@ __global__ void __launch_bounds__(kRedThreads) k_arnoldi_orth(zd* __restrict__ V
                 col[i] = pass == 0 ? t : col[i] + t;
             }
             __syncthreads();
-            for (int i0 = 0; i0 < nv; i0 += U) {
-                zd a[U][S];
-                load(i0, a);
+            auto update = [&](int i0, const zd(&a)[U][S]) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     if (i0 + u >= nv) break;
@@ -569,6 +577,12 @@ __global__ void __launch_bounds__(kRedThreads) k_arnoldi_orth(zd* __restrict__ V
 #pragma unroll
                     for (int q = 0; q < S; ++q) x[q] -= hi * a[u][q];
                 }
+            };
+            if constexpr (KEEP) update(0, first);
+            for (int i0 = KEEP ? U : 0; i0 < nv; i0 += U) {
+                zd a[U][S];
+                load(i0, a);
+                update(i0, a);
             }
         }
         double t = 0;
