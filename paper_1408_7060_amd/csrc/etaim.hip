@@ -598,7 +598,7 @@ struct Ops {
                 hipLaunchKernelGGL(k_prescale<R>, dim3(blocks_for(nB)), dim3(256), 0, c->stream, x, dinv, xs, c->ns,
                                    c->B, conj_in, gate);
             const size_t na = (size_t)c->n_anodes * c->B;
-            if (na > 0 && (c->B <= kAnterpGroupCols || na <= kAnterpGroupMax))
+            if (na > 0 && (na <= kAnterpGroupMax || (c->B <= kAnterpGroupCols && na <= kMaxBlocks256 / 2)))
                 hipLaunchKernelGGL(k_anterp_grp<R>, dim3(blocks_for(na * kAnterpLanes)), dim3(256), 0, c->stream, xs,
                                    c->anodes, c->n_anodes, c->nptr, c->nk, (const R*)c->nw_r, Q(c), g, c->B, gate);
             else if (na > 0)
