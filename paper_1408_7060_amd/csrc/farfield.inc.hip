@@ -79,12 +79,14 @@ __global__ void __launch_bounds__(128) k_far_taps(zd* __restrict__ F, const doub
         }
     }
     const size_t row = (size_t)d * NC;
+    // every tap of a direction that is not finite is not a number (its points
+    // fall outside the support, so no term would carry it)
+    const double z = 0.0 * fabs(u[0]) + 0.0 * fabs(u[1]) + 0.0 * fabs(u[2]);
     for (int tap = 0; tap < ntap; ++tap) {
         const double m = (double)(m_lo + tap);
         zd acc[NC];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) acc[c] = zd{0, 0};
-        // (a NaN direction compares false and evaluates like the others)
+        for (int c = 0; c < NC; ++c) acc[c] = zd{z, z};
         if (!(m + smax <= tb.lo() || m + smin > tb.hi())) {
 #pragma unroll
             for (int q = 0; q < 14; ++q) {
