@@ -3014,6 +3014,12 @@ constexpr size_t kFarKeep = (size_t)320 << 20;
 // of 256 compute units (more, smaller ones write more partial sums)
 constexpr int kFarBlocks = 1024;
 
+// |d|^2 of a unit vector in FP64, to this much: I - d d leaves 1 - |d|^2 of the
+// part along d, which the two transverse components do not hold, so the bound
+// is the rounding of a direction that was normalised (2 eps of |d|^2) or
+// formed from angles (some eps more)
+constexpr double kFarUnit = 16 * 2.220446049250313e-16;
+
 struct FarPlan {
     int nc = 2, ntap = 0, m_lo = 0, group = 0, M = 0;
     std::vector<double> geo, q;  // per direction: {d, P_0, P_1, P_2}, {Q_0, Q_1, Q_2}
@@ -3023,7 +3029,7 @@ void far_plan(const etaim_ctx* c, int nd, const double* dirs, FarPlan& f) {
     f.M = c->prm.nt_steps * c->B;
     for (int d = 0; d < nd; ++d) {
         const double* u = dirs + 3 * (size_t)d;
-        if (!(std::fabs(u[0] * u[0] + u[1] * u[1] + u[2] * u[2] - 1.0) < 1e-12)) f.nc = 3;
+        if (!(std::fabs(u[0] * u[0] + u[1] * u[1] + u[2] * u[2] - 1.0) <= kFarUnit)) f.nc = 3;
     }
     // |d.r| is at most the largest vertex distance from the origin for unit
     // directions (27 taps on the unit sphere at N_g = 24); other directions

@@ -11,8 +11,8 @@
 // The field is transverse, so a unit direction carries two components along
 // e1, e2 orthogonal to d; the tap table stores c = 0..nc-1 of them,
 // F_c = P_dc . sum_q ..., and U_x = sum_c Q_dcx U_c.  Where some direction is
-// not a unit vector the projection I - d d is not one onto a plane: nc = 3,
-// P = I - d d, Q = I then.
+// not a unit vector to FP64 rounding, the projection I - d d is not one onto a
+// plane: nc = 3, P = I - d d, Q = I then.
 #pragma once
 #include "aim.inc.hip"
 
