@@ -2024,8 +2024,11 @@ __global__ void __launch_bounds__(64) k_precorrect(zd* __restrict__ val, const d
 
 // a / d correctly rounded, r = the rounded 1 / d: the product with r, then
 // two corrections by the exact remainder (the first leaves the quotient
-// within one unit in the last place, the second rounds it)
+// within one unit in the last place, the second rounds it); d, r, a and the
+// quotient far from the ends of the exponent's range.  PLAIN: any a and d
+template <bool PLAIN>
 __device__ __forceinline__ double quotient(double a, double d, double r) {
+    if constexpr (PLAIN) return a / d;
     double q = a * r;
     q = fma(fma(-q, d, a), r, q);
     return fma(fma(-q, d, a), r, q);
@@ -2041,6 +2044,9 @@ __device__ __forceinline__ double quotient(double a, double d, double r) {
 // by the 14 exponentials per value (FP64 issue).  With every step's thread
 // forming phases and projections again: 3256 us a call for 100 steps x 32
 // directions x 7680 bases; this kernel 606 us.
+// PLAIN divides: for widths and delays outside the range in which the
+// quotients are known to be ordinary (excitation_launch).
+template <bool PLAIN>
 __global__ void __launch_bounds__(256) k_excitation(zd* __restrict__ V, const double* __restrict__ Sq,
                                                     const double* __restrict__ rq, const double* __restrict__ khat,
                                                     const double* __restrict__ phat, int nt, int nb, int ns, int lc,
@@ -2072,15 +2078,15 @@ __global__ void __launch_bounds__(256) k_excitation(zd* __restrict__ V, const do
         c[q] = cos(arg);
         sn[q] = -sin(arg);
     }
-    const double s2 = sigma * sigma, d2 = 2.0 * s2, i1 = 1.0 / s2, i2 = 1.0 / d2;
+    const double s2 = sigma * sigma, d2 = 2.0 * sigma * sigma, i1 = 1.0 / s2, i2 = 1.0 / d2;
     for (int l = l0; l < l1; ++l) {
         const double t = (double)(l + 1) * dt;
         double sr = 0, si = 0;
 #pragma unroll
         for (int q = 0; q < 14; ++q) {
             const double tau = t - rk[q] - td;
-            const double gg = exp(-quotient(tau * tau, d2, i2));
-            const double dg = -quotient(tau, s2, i1) * gg;
+            const double gg = exp(-quotient<PLAIN>(tau * tau, d2, i2));
+            const double dg = -quotient<PLAIN>(tau, s2, i1) * gg;
             // (dg + j w gg) (c + j s)
             sr += pr[q] * (dg * c[q] - w * gg * sn[q]);
             si += pr[q] * (dg * sn[q] + w * gg * c[q]);
