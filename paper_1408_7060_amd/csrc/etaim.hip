@@ -2529,16 +2529,26 @@ constexpr size_t kExcSteps = 32;
 // threads the excitation is spread over before a thread takes several steps
 // (a quarter of what the card holds; few steps of a small problem stay spread)
 constexpr size_t kExcThreads = 131072;
+// steps per thread for cols groups of 256 bases of a direction: at most
+// kMaxBlocks256 / cols groups of steps, so that they fit a launch
+constexpr size_t exc_steps(size_t nt, size_t cols, size_t tot) {
+    const size_t want = std::max<size_t>(1, std::min(kExcSteps, tot / kExcThreads));
+    const size_t groups = std::max<size_t>(1, kMaxBlocks256 / cols);
+    return std::max(want, (nt + groups - 1) / groups);
+}
+constexpr size_t exc_blocks(size_t nt, size_t cols, size_t lc) { return cols * ((nt + lc - 1) / lc); }
+// (4258 steps of 130000 directions of 6 bases, 53 GB: 33 steps per thread would
+// leave 130 groups of steps, and a launch holds 129)
+static_assert(exc_blocks(4258, 130000, exc_steps(4258, 130000, (size_t)4258 * 130000 * 6)) <= kMaxBlocks256, "");
+static_assert(exc_steps(100, 30 * 32, (size_t)100 * 32 * 7680) == 32 && exc_steps(5, 4, 5 * 2 * 480) == 1, "");
 
 // V from the directions and polarisations kp [2][nb][3] on the device, khat
 // the directions on the host
 int excitation_launch(etaim_ctx* c, int nb, const double* khat, const double* kp, double sigma, double td, zd* V) {
     const size_t nt = (size_t)c->prm.nt_steps, tot = nt * nb * c->ns;
     const size_t cols = (size_t)((c->ns + 255) / 256) * nb;
-    size_t lc = std::max<size_t>(1, std::min(kExcSteps, tot / kExcThreads));
     // a launch holds fewer than 2^32 threads
-    lc = std::max(lc, (cols * nt + kMaxBlocks256 - 1) / kMaxBlocks256);
-    const size_t blocks = cols * ((nt + lc - 1) / lc);
+    const size_t lc = exc_steps(nt, cols, tot), blocks = exc_blocks(nt, cols, lc);
     if (blocks > kMaxBlocks256) return fail(ETAIM_EUNSUPPORTED, "excitation: too many steps and directions for one launch");
     // the kernel's quotients tau^2 / 2 sigma^2 and tau / sigma^2 take a reciprocal
     // and its corrections, which need ordinary numbers: with the width in
