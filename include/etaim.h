@@ -173,7 +173,8 @@ typedef struct {
     double dt, h, origin[3], rmax, stencil_radius;
     int32_t ns, ng, mn, nnz, batch, precision;
     int32_t grid[3], padded[3];
-    int64_t device_bytes;
+    int64_t device_bytes; /* device memory the context holds now, work spaces kept between calls
+                             included */
 } etaim_derived;
 
 typedef struct {
@@ -287,7 +288,9 @@ int etaim_delayed_field(etaim_ctx *ctx, const void *hist, void *b);
  *               [T'(tau')/dt + j w_c T(tau')] exp(j k_c d.r') dS',
  *   tau' = l - l' + d.r'/(c dt).
  * dirs: host float64 [nd][3] unit vectors; I: device complex128
- * [N_t][B][ns]; U: device complex128 [N_t][B][nd][3]. */
+ * [N_t][B][ns]; U: device complex128 [N_t][B][nd][3].  The context keeps the
+ * work space of a call (tap table and partial sums, at most 320 MB; a larger
+ * one is freed when the call ends) for the next. */
 int etaim_farfield(etaim_ctx *ctx, int32_t nd, const double *dirs, const void *I, void *U);
 
 /* Adjoint of etaim_farfield: S = F^H Ubar, S device complex128 [N_t][B][ns]. */

@@ -3148,15 +3148,22 @@ int far_taps(etaim_ctx* c, const FarPlan& f, zd* F, const double* geo, int d0, i
     return ETAIM_OK;
 }
 
+// the far-field work space goes back (device_bytes counts it while it is kept)
+int far_release(etaim_ctx* c) {
+    if (c->farws) HIPCHK(hipFree(c->farws));
+    c->farws = nullptr;
+    c->dev_bytes -= (int64_t)c->farws_bytes;
+    c->farws_bytes = 0;
+    return ETAIM_OK;
+}
 // far-field work space of at least `bytes` (kept between calls up to kFarKeep)
 int far_space(etaim_ctx* c, size_t bytes) {
     if (c->farws_bytes >= bytes) return ETAIM_OK;
-    if (c->farws) HIPCHK(hipFree(c->farws));
-    c->farws = nullptr;
-    c->farws_bytes = 0;
+    CHK(far_release(c));
     if (hipMalloc(&c->farws, bytes) != hipSuccess)
         return fail(ETAIM_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
     c->farws_bytes = bytes;
+    c->dev_bytes += (int64_t)bytes;
     return ETAIM_OK;
 }
 
@@ -3208,11 +3215,7 @@ int far_run(etaim_ctx* c, int nd, const double* dirs, const zd* in, zd* out, boo
     }
     // the direction arrays on the host and the work space are free after this
     HIPCHK(hipStreamSynchronize(c->stream));
-    if (c->farws_bytes > kFarKeep) {
-        HIPCHK(hipFree(c->farws));
-        c->farws = nullptr;
-        c->farws_bytes = 0;
-    }
+    if (c->farws_bytes > kFarKeep) CHK(far_release(c));
     return ETAIM_OK;
 }
 
