@@ -405,10 +405,18 @@ typedef struct {
                                 the z lines first and hold two tiles instead of four, 3 separate
                                 y- and z-line passes over a full-spectrum work array (any grid whose
                                 lines fit the LDS line kernel; chosen by itself where the padded
-                                plane does not fit the LDS) */
-    int32_t x_engine;        /* x stage: 0 LDS-staged lines with the anterpolation fused in,
-                                1 register-resident lines after a separate anterpolation
-                                (needs N_x in {16, 24, 48}) */
+                                plane does not fit the LDS).  With 0 and 3 the matvec of some planes
+                                runs in one kernel of its own, whatever the plans, and the engine
+                                holds for the commit and the history sum: N_y = N_z in {18, 27, 32,
+                                36, 54, 64}, in FP32 also 96; N_z = 8 with N_y in {16, 24, 48}, in
+                                FP32 also 96.  That kernel reads a second copy of the Green table
+                                (as engines 1 and 2 do), in device_bytes */
+    int32_t x_engine;        /* x stage: 0 LDS-staged lines with the anterpolation fused in (N_x in
+                                {18, 27, 32, 36, 54, 64}: the stage of 1, which takes neither
+                                radix[0] nor gather_rows nor lines_per_block there), 1 register-
+                                resident lines after a separate anterpolation (needs N_x in {16, 24,
+                                48}, or a padded length with four-step lines: 144, 192, 288, 384,
+                                576) */
     int32_t guess_order;     /* GMRES initial guess of step l: the polynomial through the last
                                 p solutions evaluated at step l, p <= guess_order chosen as the
                                 order that best predicted step l-1 (0: zero guess, 1: the
@@ -438,6 +446,10 @@ typedef struct {
  * random vector; GMRES solves of a seeded right-hand side with zero history),
  * checks each candidate's matvec against the current setting (relative L2
  * <= 1e-4 in FP32, 1e-10 in FP64; others are skipped), and keeps the fastest.
+ * Where the matvec does not depend on the y/z engine and plans (the grids that
+ * yz_engine lists), these are ranked by a commit and a history sum instead;
+ * radix[0], gather_rows and lines_per_block stay as they are where the
+ * register x stage takes none of them.
  * budget_ms bounds the timing work (>= 1; candidates are tried in order of
  * expected benefit).  cache_path (host string or NULL): a JSON-lines file; a
  * record whose key matches this problem's shape (precision, batch, ns,

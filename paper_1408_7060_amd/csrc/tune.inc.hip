@@ -292,9 +292,10 @@ int cache_append(const char* path, const std::string& key, const etaim_tuning& t
 // ---- timing
 struct TuneBufs {
     zd *x = nullptr, *y = nullptr, *rhs = nullptr, *sol = nullptr;
+    void* slot = nullptr;  // a spectrum slot for timed commits
     hipEvent_t e0 = nullptr, e1 = nullptr;
     ~TuneBufs() {
-        for (zd* p : {x, y, rhs, sol})
+        for (void* p : {(void*)x, (void*)y, (void*)rhs, (void*)sol, slot})
             if (p) (void)hipFree(p);
         if (e0) (void)hipEventDestroy(e0);
         if (e1) (void)hipEventDestroy(e1);
@@ -346,6 +347,32 @@ int time_delayed(etaim_ctx* c, TuneBufs& b, double& ms) {
     HIPCHK(hipEventElapsedTime(&t, b.e0, b.e1));
     ms = t / k;
     set_far_r0(c, -1);
+    return ETAIM_OK;
+}
+
+// a time step's work on the history: a commit (into a slot of its own: the
+// ring keeps the march's) and a history sum.  The commit is left out where
+// there is no memory for the slot
+template <typename R>
+int time_history(etaim_ctx* c, TuneBufs& b, double& ms) {
+    const int k = 8;
+    double d_ms = 0;
+    CHK(time_delayed<R>(c, b, d_ms));
+    ms = d_ms;
+    if (!b.slot && hipMalloc(&b.slot, (size_t)4 * c->B * c->Np * sizeof(cplx<R>)) != hipSuccess) {
+        b.slot = nullptr;
+        (void)hipGetLastError();
+        return ETAIM_OK;
+    }
+    cplx<R>* slot = (cplx<R>*)b.slot;
+    CHK(Ops<R>::commit_slot(c, slot, b.x));
+    HIPCHK(hipEventRecord(b.e0, c->stream));
+    for (int i = 0; i < k; ++i) CHK(Ops<R>::commit_slot(c, slot, b.x));
+    HIPCHK(hipEventRecord(b.e1, c->stream));
+    HIPCHK(hipEventSynchronize(b.e1));
+    float t = 0;
+    HIPCHK(hipEventElapsedTime(&t, b.e0, b.e1));
+    ms += t / k;
     return ETAIM_OK;
 }
 
@@ -420,11 +447,29 @@ int autotune_impl(etaim_ctx* c, int budget_ms, etaim_tuning* out) {
         put_shape(c, best);
         return ETAIM_OK;
     };
+    // where the products run on the plane kernel, no launch of theirs takes the
+    // y/z engine (0 or 3) and its plans: they are ranked by the history's work
+    const bool by_history = plane_kernel(c);
+    double h_best = 0;
+    if (by_history) CHK(time_history<R>(c, b, h_best));
+    auto trial_yz = [&](const Shape& s) -> int {
+        if (!by_history) return trial(s);
+        if (!shape_fits<R>(c, s) || spent() > budget_ms) return ETAIM_OK;
+        put_shape(c, s);
+        double t = 0;
+        CHK(time_history<R>(c, b, t));
+        if (t < h_best) {
+            h_best = t;
+            best = s;
+        }
+        put_shape(c, best);
+        return ETAIM_OK;
+    };
     for (int eng : {0, 1, 2, 3})
         if (eng != best.engine) {
             Shape s = best;
             s.engine = eng;
-            CHK(trial(s));
+            CHK(trial_yz(s));
         }
     for (int eng : {0, 1})
         if (eng != best.xeng) {
@@ -432,34 +477,39 @@ int autotune_impl(etaim_ctx* c, int budget_ms, etaim_tuning* out) {
             s.xeng = eng;
             CHK(trial(s));
         }
-    for (const Radix& p : candidate_plans(c->gd.L[0]))
-        if (!radix_equal(p, best.rx)) {
-            Shape s = best;
-            s.rx = p;
-            s.mr = s.mt = 0;
-            CHK(trial(s));
-        }
+    // the register x lines take neither plan nor rows
+    const bool x_plans = !xreg(c);
+    if (x_plans)
+        for (const Radix& p : candidate_plans(c->gd.L[0]))
+            if (!radix_equal(p, best.rx)) {
+                Shape s = best;
+                s.rx = p;
+                s.mr = s.mt = 0;
+                CHK(trial(s));
+            }
     for (const Radix& p : candidate_plans(c->gd.L[1]))
         if (!radix_equal(p, best.ry)) {
             Shape s = best;
             s.ry = p;
-            CHK(trial(s));
+            CHK(trial_yz(s));
         }
     for (const Radix& p : candidate_plans(c->gd.L[2]))
         if (!radix_equal(p, best.rz)) {
             Shape s = best;
             s.rz = p;
+            CHK(trial_yz(s));
+        }
+    if (x_plans) {
+        for (int mr : {1, 2, 4, 8, 16, 32}) {
+            Shape s = best;
+            s.mr = mr;
             CHK(trial(s));
         }
-    for (int mr : {1, 2, 4, 8, 16, 32}) {
-        Shape s = best;
-        s.mr = mr;
-        CHK(trial(s));
-    }
-    for (int mt : {2, 4, 8, 16, 32, 64}) {
-        Shape s = best;
-        s.mt = mt;
-        CHK(trial(s));
+        for (int mt : {2, 4, 8, 16, 32, 64}) {
+            Shape s = best;
+            s.mt = mt;
+            CHK(trial(s));
+        }
     }
     for (int w : {1, 2, 4}) {
         Shape s = best;
