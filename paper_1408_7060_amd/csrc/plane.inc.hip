@@ -16,8 +16,8 @@
 // rows take, per parity py, the forward DFT, the Green product and the inverse
 // DFT, summed over py into the tile; the inverse z lines add to the result,
 // which is stored in place at the end.  The plane is read and written once;
-// the tile for one or both pz (TZ) is all the LDS a block needs: N = 96 in
-// FP32 takes 77 KB, two blocks per CU.  Bound by FP32 (FP64) issue and, for
+// the tiles of both pz (and the twiddles) are all the LDS a block needs: N = 96
+// in FP32 takes 157 KB, one block per CU.  Bound by FP32 (FP64) issue and, for
 // small planes, by latency.
 #pragma once
 #include "aim.inc.hip"
@@ -32,19 +32,15 @@ template <typename R, int NY, int PY, int NZ>
 __host__ __device__ constexpr size_t plane_tile() {
     return (size_t)NZ * plane_ld(NY, PY) * sizeof(cplx<R>);
 }
-// both parities' tiles at once where they fit the LDS: the threads double and
-// each half takes one pz (half), so that a block holds twice the waves and
-// no partial result waits in registers.  On flat planes, whose rows occupy a
-// wave either way, each thread takes its column for one pz after the other
-// (48x8 in FP64: 50 us for 8 columns, 59 with halves; the cubes 10 to 30 %
-// faster with halves at one column, equal at eight)
-template <typename R, int NY, int PY, int NZ>
-__host__ __device__ constexpr int plane_tz() {
-    return 2 * plane_tile<R, NY, PY, NZ>() <= 156 * 1024 ? 2 : 1;
-}
+// both parities' tiles are in the LDS at once; the threads double and each half
+// takes one pz (half), so that a block holds twice the waves and no partial
+// result waits in registers.  On flat planes, whose rows occupy a wave either
+// way, each thread takes its column for one pz after the other (48x8 in FP64:
+// 50 us for 8 columns, 59 with halves; the cubes 10 to 30 % faster with halves
+// at one column, equal at eight)
 template <typename R, int NY, int PY, int NZ>
 __host__ __device__ constexpr bool plane_half() {
-    return plane_tz<R, NY, PY, NZ>() == 2 && (NZ > 8 || 2 * plane_tile<R, NY, PY, NZ>() > 72 * 1024);
+    return NZ > 8 || 2 * plane_tile<R, NY, PY, NZ>() > 72 * 1024;
 }
 // threads: a lane for every (column, p) of the z lines, whole waves
 template <typename R, int NY, int PY, int NZ, int PZ>
@@ -53,7 +49,7 @@ __host__ __device__ constexpr int plane_threads() {
 }
 template <typename R, int NY, int PY, int NZ>
 __host__ __device__ constexpr size_t plane_lds_bytes() {
-    return plane_tz<R, NY, PY, NZ>() * plane_tile<R, NY, PY, NZ>() + (size_t)(2 * NY + 2 * NZ) * sizeof(cplx<R>);
+    return 2 * plane_tile<R, NY, PY, NZ>() + (size_t)(2 * NY + 2 * NZ) * sizeof(cplx<R>);
 }
 
 // the twiddles between the steps, [par][p][k1], from w_{2N}^n: a lane reads
@@ -152,12 +148,13 @@ __attribute__((amdgpu_waves_per_eu(plane_waves<R, NY, PY, NZ, PZ>()))) k_plane_g
                                                                           GridDims g, int conj_g,
                                                                           const int* __restrict__ gate) {
     if (gated_off(gate)) return;
-    constexpr int QY = NY / PY, QZ = NZ / PZ, LD = plane_ld(NY, PY), TZ = plane_tz<R, NY, PY, NZ>();
+    constexpr int QY = NY / PY, QZ = NZ / PZ, LD = plane_ld(NY, PY);
     constexpr int T = plane_threads<R, NY, PY, NZ, PZ>(), CW = 64 / PZ, RW = 64 / PY;
     static_assert(QY * PY == NY && QZ * PZ == NZ && QY % PY == 0 && QZ % PZ == 0, "line split");
+    static_assert(plane_lds_bytes<R, NY, PY, NZ>() <= 160 * 1024, "the tiles of both parities fit the LDS");
     extern __shared__ unsigned char smem_raw[];
     cplx<R>* tile = reinterpret_cast<cplx<R>*>(smem_raw);
-    cplx<R>* twy = tile + (size_t)TZ * NZ * LD;
+    cplx<R>* twy = tile + (size_t)2 * NZ * LD;
     cplx<R>* twz = twy + 2 * NY;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     mline_table<R, PY, QY>(twy, twy_g);
@@ -182,93 +179,88 @@ __attribute__((amdgpu_waves_per_eu(plane_waves<R, NY, PY, NZ, PZ>()))) k_plane_g
         for (int j = 0; j < QZ; ++j) in[j] = zlive ? pl[(zp + PZ * j) * NY + y] : cplx<R>{0, 0};
     }
     __syncthreads();
-    for (int pz0 = 0; pz0 < 2; pz0 += TZ) {
 #pragma unroll 1
-        for (int t = hz; t < (HALF ? hz + 1 : TZ); ++t) {
-            const int pz = TZ == 2 ? t : pz0;
-            cplx<R> u[QZ];
+    for (int pz = hz; pz < (HALF ? hz + 1 : 2); ++pz) {
+        cplx<R> u[QZ];
 #pragma unroll
-            for (int j = 0; j < QZ; ++j) u[j] = KEEP ? in[KEEP ? j : 0] : zlive ? pl[(zp + PZ * j) * NY + y] : cplx<R>{0, 0};
-            cplx<R>* col = tile + (size_t)t * NZ * LD + y;
-            mline_fwd<R, PZ, QZ>(u, zp, pz, col, LD, twz + (pz * PZ + (zlive ? zp : 0)) * QZ, zlive);
-            if (zlive) {
-#pragma unroll
-                for (int i = 0; i < QZ / PZ; ++i)
-#pragma unroll
-                    for (int q = 0; q < PZ; ++q) col[(zp + PZ * i + QZ * q) * LD] = u[i * PZ + q];
-            }
-        }
-        __syncthreads();
-        // rows kz' of the tiles: RW rows per wave, their PY lanes adjacent
-        constexpr int ROUNDS = (TZ * NZ + RW - 1) / RW;
-        for (int rd = wave; rd < ROUNDS; rd += T / 64) {
-            const int p = lane % PY, row = rd * RW + lane / PY;
-            const bool live = lane < RW * PY && row < TZ * NZ;
-            const int t = TZ == 2 ? (row >= NZ ? 1 : 0) : 0, kz = row - t * NZ, pz = TZ == 2 ? t : pz0;
-            const int zf = live ? fold(2 * kz + pz, 2 * NZ) : 0;
-            cplx<R>* rp = tile + (size_t)(live ? row : 0) * LD;
-            const unsigned up = (unsigned)(2 * p * (NZ + 1) + zf), down = (unsigned)(2 * (PY - 1 - p) * (NZ + 1) + zf);
-            // row x times w_{2N}^{py y}: DFT, Green product, inverse DFT, post-twiddle
-            auto pass = [&](cplx<R>(&x)[QY], int py) {
-                // ky = 2 c + py of c = c0 + p: a group of PY lanes lies on one side of
-                // the fold at c = N_y / 2 (PY divides it), so that its address is a
-                // uniform row plus the lane's offset up or down
-                auto green = [&](int c0) -> cplx<R> {
-                    if constexpr (NY % (2 * PY) != 0)
-                        return Gk[fold(2 * (c0 + p) + py, 2 * NY) * (NZ + 1) + zf];
-                    else if (2 * c0 < NY)
-                        return (Gk + (2 * c0 + py) * (NZ + 1))[up];
-                    else
-                        return (Gk + (2 * NY - 2 * (c0 + PY - 1) - py) * (NZ + 1))[down];
-                };
-                // short lines: the Green values wait in registers
-                constexpr bool AHEAD = QY <= 12;
-                cplx<R> gr[AHEAD ? QY : 1];
-                if constexpr (AHEAD) {
-#pragma unroll
-                    for (int i = 0; i < QY; ++i) gr[i] = green(PY * (i / PY) + QY * (i % PY));
-                }
-                mline_fwd<R, PY, QY>(x, p, py, rp, 1, twy + (py * PY + p) * QY, live);
-#pragma unroll
-                for (int i = 0; i < QY; ++i) {
-                    cplx<R> gv = AHEAD ? gr[AHEAD ? i : 0] : green(PY * (i / PY) + QY * (i % PY));
-                    if (conj_g) gv.y = -gv.y;
-                    x[i] = cmul_fma(x[i], gv);
-                }
-                mline_inv<R, PY, QY>(x, p, py, rp, 1, twy + (py * PY + p) * QY, live);
-            };
-            // py = 1 on a copy of the row (its LDS is the exchange's space),
-            // then py = 0, one after the other in the registers
-            cplx<R> u[QY], v[QY];
-#pragma unroll
-            for (int j = 0; j < QY; ++j) v[j] = u[j] = live ? rp[p + PY * j] : cplx<R>{0, 0};
-            wave_sync();
-            pass(v, 1);
-            __builtin_amdgcn_sched_barrier(0);
-            pass(u, 0);
-#pragma unroll
-            for (int j = 0; j < QY; ++j) v[j] += u[j];
-            if (live) {
-#pragma unroll
-                for (int j = 0; j < QY; ++j) rp[p + PY * j] = v[j];
-            }
-        }
-        __syncthreads();
-#pragma unroll 1
-        for (int t = hz; t < (HALF ? hz + 1 : TZ); ++t) {
-            const int pz = TZ == 2 ? t : pz0;
-            cplx<R> u[QZ];
-            cplx<R>* col = tile + (size_t)t * NZ * LD + y;
+        for (int j = 0; j < QZ; ++j) u[j] = KEEP ? in[KEEP ? j : 0] : zlive ? pl[(zp + PZ * j) * NY + y] : cplx<R>{0, 0};
+        cplx<R>* col = tile + (size_t)pz * NZ * LD + y;
+        mline_fwd<R, PZ, QZ>(u, zp, pz, col, LD, twz + (pz * PZ + (zlive ? zp : 0)) * QZ, zlive);
+        if (zlive) {
 #pragma unroll
             for (int i = 0; i < QZ / PZ; ++i)
 #pragma unroll
-                for (int q = 0; q < PZ; ++q) u[i * PZ + q] = zlive ? col[(zp + PZ * i + QZ * q) * LD] : cplx<R>{0, 0};
-            wave_sync();
-            mline_inv<R, PZ, QZ>(u, zp, pz, col, LD, twz + (pz * PZ + (zlive ? zp : 0)) * QZ, zlive);
-#pragma unroll
-            for (int j = 0; j < QZ; ++j) acc[j] = HALF ? u[j] : acc[j] + u[j];
+                for (int q = 0; q < PZ; ++q) col[(zp + PZ * i + QZ * q) * LD] = u[i * PZ + q];
         }
-        if (TZ == 1) __syncthreads();
+    }
+    __syncthreads();
+    // rows kz' of the tiles: RW rows per wave, their PY lanes adjacent
+    constexpr int ROUNDS = (2 * NZ + RW - 1) / RW;
+    for (int rd = wave; rd < ROUNDS; rd += T / 64) {
+        const int p = lane % PY, row = rd * RW + lane / PY;
+        const bool live = lane < RW * PY && row < 2 * NZ;
+        const int pz = row >= NZ ? 1 : 0, kz = row - pz * NZ;
+        const int zf = live ? fold(2 * kz + pz, 2 * NZ) : 0;
+        cplx<R>* rp = tile + (size_t)(live ? row : 0) * LD;
+        const unsigned up = (unsigned)(2 * p * (NZ + 1) + zf), down = (unsigned)(2 * (PY - 1 - p) * (NZ + 1) + zf);
+        // row x times w_{2N}^{py y}: DFT, Green product, inverse DFT, post-twiddle
+        auto pass = [&](cplx<R>(&x)[QY], int py) {
+            // ky = 2 c + py of c = c0 + p: a group of PY lanes lies on one side of
+            // the fold at c = N_y / 2 (PY divides it), so that its address is a
+            // uniform row plus the lane's offset up or down
+            auto green = [&](int c0) -> cplx<R> {
+                if constexpr (NY % (2 * PY) != 0)
+                    return Gk[fold(2 * (c0 + p) + py, 2 * NY) * (NZ + 1) + zf];
+                else if (2 * c0 < NY)
+                    return (Gk + (2 * c0 + py) * (NZ + 1))[up];
+                else
+                    return (Gk + (2 * NY - 2 * (c0 + PY - 1) - py) * (NZ + 1))[down];
+            };
+            // short lines: the Green values wait in registers
+            constexpr bool AHEAD = QY <= 12;
+            cplx<R> gr[AHEAD ? QY : 1];
+            if constexpr (AHEAD) {
+#pragma unroll
+                for (int i = 0; i < QY; ++i) gr[i] = green(PY * (i / PY) + QY * (i % PY));
+            }
+            mline_fwd<R, PY, QY>(x, p, py, rp, 1, twy + (py * PY + p) * QY, live);
+#pragma unroll
+            for (int i = 0; i < QY; ++i) {
+                cplx<R> gv = AHEAD ? gr[AHEAD ? i : 0] : green(PY * (i / PY) + QY * (i % PY));
+                if (conj_g) gv.y = -gv.y;
+                x[i] = cmul_fma(x[i], gv);
+            }
+            mline_inv<R, PY, QY>(x, p, py, rp, 1, twy + (py * PY + p) * QY, live);
+        };
+        // py = 1 on a copy of the row (its LDS is the exchange's space),
+        // then py = 0, one after the other in the registers
+        cplx<R> u[QY], v[QY];
+#pragma unroll
+        for (int j = 0; j < QY; ++j) v[j] = u[j] = live ? rp[p + PY * j] : cplx<R>{0, 0};
+        wave_sync();
+        pass(v, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        pass(u, 0);
+#pragma unroll
+        for (int j = 0; j < QY; ++j) v[j] += u[j];
+        if (live) {
+#pragma unroll
+            for (int j = 0; j < QY; ++j) rp[p + PY * j] = v[j];
+        }
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int pz = hz; pz < (HALF ? hz + 1 : 2); ++pz) {
+        cplx<R> u[QZ];
+        cplx<R>* col = tile + (size_t)pz * NZ * LD + y;
+#pragma unroll
+        for (int i = 0; i < QZ / PZ; ++i)
+#pragma unroll
+            for (int q = 0; q < PZ; ++q) u[i * PZ + q] = zlive ? col[(zp + PZ * i + QZ * q) * LD] : cplx<R>{0, 0};
+        wave_sync();
+        mline_inv<R, PZ, QZ>(u, zp, pz, col, LD, twz + (pz * PZ + (zlive ? zp : 0)) * QZ, zlive);
+#pragma unroll
+        for (int j = 0; j < QZ; ++j) acc[j] = HALF ? u[j] : acc[j] + u[j];
     }
     if constexpr (HALF) {
         // pz = 1's half hands its columns over in its own tile
