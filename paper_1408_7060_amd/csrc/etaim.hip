@@ -3131,9 +3131,13 @@ int far_gemm(etaim_ctx* c, const zd* A, const zd* F, zd* out, const FarPlan& f, 
     return ETAIM_OK;
 }
 
-// the tap table of directions d0 .. d0 + n - 1
+// the tap table of directions d0 .. d0 + n - 1, its taps shared out between nz
+// threads per (direction, basis) where those alone are fewer than kFarTapThreads
+constexpr size_t kFarTapThreads = 65536;
 int far_taps(etaim_ctx* c, const FarPlan& f, zd* F, const double* geo, int d0, int n) {
-    const dim3 grid((unsigned)((c->ns + 127) / 128), (unsigned)n);
+    const size_t want = kFarTapThreads / ((size_t)n * c->ns);
+    const int nz = (int)std::max<size_t>(1, std::min({want, (size_t)f.ntap, kMaxGridY}));
+    const dim3 grid((unsigned)((c->ns + 127) / 128), (unsigned)n, (unsigned)nz);
     const double w = 2.0 * kPi * c->prm.fc, mu4pi = kMu0 / (4.0 * kPi);
 #define ETAIM_TAPS(NC, BL)                                                                                          \
     hipLaunchKernelGGL((k_far_taps<NC, BL>), grid, dim3(128), 0, c->stream, F, c->Sq, c->rq, geo + 12 * (size_t)d0, \

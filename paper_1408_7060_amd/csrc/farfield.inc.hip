@@ -20,38 +20,102 @@ namespace etaim {
 
 typedef double dx4 __attribute__((ext_vector_type(4)));
 
-// T and T' at tau; false outside the support.  The CPPIF's four pieces (as
-// cppif_piece) from their coefficients, without its divisions and loops.
-template <bool BLIF>
-__device__ __forceinline__ bool far_basis(const TBasis& tb, double tau, double& T0, double& T1) {
-    if constexpr (BLIF) {
-        double d[4];
-        const bool in = tb.eval(tau, d);
-        T0 = d[0];
-        T1 = d[1];
-        return in;
+// The CPPIF and its derivative at tau; false outside the support.  Its four
+// pieces (as cppif_piece) from their coefficients, without its divisions and
+// loops.
+__device__ __forceinline__ bool far_cppif(double tau, double& T0, double& T1) {
+    if (!(tau > -1.0 && tau <= (double)kQ)) return false;
+    const double p = ceil(tau), s = tau - p;
+    const int i = (int)p;
+    const double e1 = 6.0 - p, e2 = i == 0 ? 11.0 : i == 1 ? 6.0 : i == 2 ? 3.0 : 2.0, e3 = i == 0 ? 6.0 : 0.0;
+    const double r = i == 0 ? 1.0 / 6.0 : i == 1 ? -0.5 : i == 2 ? 0.5 : -1.0 / 6.0;
+    T0 = (((s + e1) * s + e2) * s + e3) * r;
+    T1 = ((3.0 * s + 2.0 * e1) * s + e2) * r;
+    return true;
+}
+
+// (-1)^j / (2j+1)!
+struct FarSinc {
+    double c[16];
+};
+__host__ __device__ constexpr FarSinc far_sinc() {
+    FarSinc f{};
+    double v = 1.0;
+    for (int j = 0; j < 16; ++j) {
+        if (j > 0) v /= -(2.0 * j) * (2.0 * j + 1.0);
+        f.c[j] = v;
+    }
+    return f;
+}
+
+// The BLIF and its derivative at tau (TBasis::blif_at without its second and
+// third derivatives and, near tau = 0, its powers: 16 terms of the sinc's
+// series by Horner's rule in (pi tau)^2)
+__device__ __forceinline__ bool far_blif(const TBasis& tb, double tau, double& T0, double& T1) {
+    if (!(tau > tb.lo() && tau <= tb.hi())) return false;
+    const double MM = (double)tb.M * (double)tb.M, u = 1.0 - tau * tau / MM, u1 = -2.0 * tau / MM;
+    double w0 = 0, w1 = 0;
+    for (int k = kBlifTerms - 1; k >= 0; --k) {
+        w0 = w0 * u + tb.c[k];
+        if (k >= 1) w1 = w1 * u + tb.c[k] * (double)k;
+    }
+    const double x = kPi * tau, x2 = x * x;
+    double S0, S1;
+    if (fabs(tau) < 0.25) {
+        // sin x / x = sum_j (-x2)^j / (2j+1)!, its x-derivative x sum_j 2 (j+1) (-1)^(j+1) x2^j / (2j+3)!
+        constexpr FarSinc f = far_sinc();
+        S0 = S1 = 0;
+#pragma unroll
+        for (int j = 15; j >= 0; --j) {
+            S0 = S0 * x2 + f.c[j];
+            if (j >= 1) S1 = S1 * x2 + f.c[j] * (2.0 * (double)j);
+        }
+        S1 = kPi * x * S1;
     } else {
-        if (!(tau > -1.0 && tau <= (double)kQ)) return false;
-        const double p = ceil(tau), s = tau - p;
-        const int i = (int)p;
-        const double e1 = 6.0 - p, e2 = i == 0 ? 11.0 : i == 1 ? 6.0 : i == 2 ? 3.0 : 2.0, e3 = i == 0 ? 6.0 : 0.0;
-        const double r = i == 0 ? 1.0 / 6.0 : i == 1 ? -0.5 : i == 2 ? 0.5 : -1.0 / 6.0;
-        T0 = (((s + e1) * s + e2) * s + e3) * r;
-        T1 = ((3.0 * s + 2.0 * e1) * s + e2) * r;
-        return true;
+        double sx, cx;
+        sincos(x, &sx, &cx);
+        S0 = sx / x;
+        S1 = kPi * (x * cx - sx) / x2;
+    }
+    T0 = S0 * w0;
+    T1 = S1 * w0 + S0 * (w1 * u1);
+    return true;
+}
+
+// where a tap's sums start: 0, but NaN for a direction that is not finite (its
+// points fall outside the support, so no term would carry it)
+__device__ __forceinline__ double far_zero(const double* u) {
+    return 0.0 * fabs(u[0]) + 0.0 * fabs(u[1]) + 0.0 * fabs(u[2]);
+}
+
+// acc[c] += g[c][q] (a + j b) (cs + j sn), a = T'/dt, b = w T
+template <int NC, size_t NQ>
+__device__ __forceinline__ void far_term(zd (&acc)[NC], const double (&g)[NC][NQ], int q, double a, double b,
+                                         double cs, double sn) {
+    const double fr = a * cs - b * sn;
+    const double fi = a * sn + b * cs;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        acc[c].x += g[c][q] * fr;
+        acc[c].y += g[c][q] * fi;
     }
 }
 
 // Tap table F[tap][d nc + c][k] =
 //   -(mu/4pi) sum_q (P_dc . Sq[k][q]) [T'(tau)/dt + j w T(tau)] exp(j kc d.r_q),
 //   tau = (m_lo + tap) + d.r_q/(c dt);
-// geo[d] = {d, P_d0, P_d1, P_d2}.  A thread owns one (d, k) and every tap:
-// the 14 phases and projections do not depend on the tap and stay in
+// geo[d] = {d, P_d0, P_d1, P_d2}.  A thread owns one (d, k) and every nz-th
+// tap: the 14 phases and projections do not depend on the tap and stay in
 // registers, and the taps outside the basis's support (all but 5 or 6, of
 // 27 at N_g = 24) only store zeros.  Bound by the store of the table.  With
 // a thread per (tap, d, k), each evaluating the phases again, and the range
 // of the cube around the object (43 taps on the unit sphere): 2490 us for 64
-// directions x 7680 bases; this kernel 2 x 173 us (27 taps).
+// directions x 7680 bases; this kernel 2 x 173 us (27 taps).  Few directions
+// leave most of the card idle, with a chain of every tap on each thread: the
+// blocks' third index then shares the taps out (one direction of 480 bases, 7
+// taps: 16 -> 9 us; of 7680 bases, 27 taps: 63 -> 22 us).  The BLIF's table took
+// 520 us for 480 bases and 9 taps with every tap on a thread and the sinc's
+// series by powers, 286 with a thread per tap, 17 this way.
 template <int NC, bool BLIF>
 __global__ void __launch_bounds__(128) k_far_taps(zd* __restrict__ F, const double* __restrict__ Sq,
                                                   const double* __restrict__ rq, const double* __restrict__ geo,
@@ -79,10 +143,8 @@ __global__ void __launch_bounds__(128) k_far_taps(zd* __restrict__ F, const doub
         }
     }
     const size_t row = (size_t)d * NC;
-    // every tap of a direction that is not finite is not a number (its points
-    // fall outside the support, so no term would carry it)
-    const double z = 0.0 * fabs(u[0]) + 0.0 * fabs(u[1]) + 0.0 * fabs(u[2]);
-    for (int tap = 0; tap < ntap; ++tap) {
+    const double z = far_zero(u);
+    for (int tap = blockIdx.z; tap < ntap; tap += gridDim.z) {
         const double m = (double)(m_lo + tap);
         zd acc[NC];
 #pragma unroll
@@ -91,16 +153,8 @@ __global__ void __launch_bounds__(128) k_far_taps(zd* __restrict__ F, const doub
 #pragma unroll
             for (int q = 0; q < 14; ++q) {
                 double T0, T1;
-                if (!far_basis<BLIF>(tb, m + s[q], T0, T1)) continue;
-                // (T'/dt + j w T) (c + j s)
-                const double a = T1 * idt, b = w * T0;
-                const double fr = a * cs[q] - b * sn[q];
-                const double fi = a * sn[q] + b * cs[q];
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    acc[c].x += g[c][q] * fr;
-                    acc[c].y += g[c][q] * fi;
-                }
+                if (!(BLIF ? far_blif(tb, m + s[q], T0, T1) : far_cppif(m + s[q], T0, T1))) continue;
+                far_term<NC>(acc, g, q, T1 * idt, w * T0, cs[q], sn[q]);
             }
         }
 #pragma unroll
