@@ -166,74 +166,83 @@ __global__ void __launch_bounds__(128) k_far_taps(zd* __restrict__ F, const doub
 // r < M, kk < K, n < N; rows of A outside [0, M) are zero.
 //   ADJ = false: A = I [M][K = ns], sh = -B, op(F)[tap][kk][n] = F[tap][n][kk]
 //   ADJ = true:  A = W [M][K = ncol], sh = +B, op(F)[tap][kk][n] = conj(F[tap][kk][n])
-// A block of four waves owns 64 rows x 64 columns, a wave 32 x 32 as 2 x 2
-// complex tiles of v_mfma_f64_16x16x4 (four real products each).  The K loop
-// runs over groups of 8 kk (outer) and taps (inner), so that the taps of a
-// group read the same columns of A, shifted by B rows, from cache; a step's
-// 8 x 64 pieces of A and F go through LDS, the next step's loads in flight
-// during its 32 products per wave.  Bound by the matrix cores (66.6 TFLOP/s
-// in a large FP64 product on this card).  The steps are split over nsplit
-// blocks where the tiles alone would leave compute units idle (part[split]
-// then, summed in order by the callers' kernels).  The running sums are
-// added to a second set every kFlush steps, so that a chain of additions
-// stays at 8 kFlush products.
+// A block of four waves owns TR rows x TC columns: 64 x 64, a wave 32 x 32 as
+// 2 x 2 complex tiles of v_mfma_f64_16x16x4 (four real products each); for up
+// to 16 columns (8 directions, forward) 128 x 16, a wave 32 x 16, whose tiles of
+// rows past M are left out.  The K loop runs over groups of 8 kk (outer) and
+// taps (inner), so that the taps of a group read the same columns of A, shifted
+// by B rows, from cache; a step's pieces of A and F go through LDS, the next
+// step's loads in flight during its products (32 per wave, 16 of a narrow
+// tile).  Bound by the matrix cores (66.6 TFLOP/s in a large FP64 product on
+// this card).  The steps are split over nsplit blocks where the tiles alone
+// would leave compute units idle (part[split] then, summed in order by the
+// callers' kernels).  The running sums are added to a second set every kFlush
+// steps, so that a chain of additions stays at 8 kFlush products.
 // One block per output element with every thread on the same (r, n), each
 // element reading all of F and I again: 100.9 ms for 640 rows, 64 directions
 // and 43 taps of 7680 bases; this kernel 2 x 1.15 ms (27 taps), 49 TFLOP/s.
-constexpr int kFarTile = 64, kFarK = 8, kFlush = 64;
+// One direction, 19200 rows of 480 bases: 255 us that way, 641 with 64 x 64,
+// 233 with 128 x 16.
+constexpr int kFarTile = 64, kFarNarrow = 16, kFarK = 8, kFlush = 64;
+__host__ __device__ constexpr int far_rows(int tc) { return tc == kFarNarrow ? 128 : kFarTile; }
 
-template <bool ADJ>
+template <bool ADJ, int TC>
 __global__ void __launch_bounds__(256, 2) k_far_gemm(const zd* __restrict__ A, const zd* __restrict__ F,
                                                      zd* __restrict__ out, int M, int N, int K, int ntap, int m_lo,
                                                      int B, int mt, int nt, int nsplit, int add) {
     constexpr int LD = kFarK + 1;  // odd row length in 16-byte units: lanes on consecutive rows spread over the banks
-    __shared__ zd sA[2][kFarTile * LD], sB[2][kFarTile * LD];
+    constexpr int TR = far_rows(TC), NJ = TC == kFarNarrow ? 1 : 2, LA = TR / 32;
+    static_assert(TC == kFarTile || (TC == kFarNarrow && !ADJ), "tile");
+    __shared__ zd sA[2][TR * LD], sB[2][TC * LD];
     // row tiles fastest within one run of blocks per XCD (round-robin
     // dispatch): the blocks that read one piece of F share an L2
     const int per = gridDim.x / kXcds;
     const int lb = (int)(blockIdx.x % kXcds) * per + (int)(blockIdx.x / kXcds);
     if (lb >= mt * nt * nsplit) return;
     const int rt = lb % mt, ct = (lb / mt) % nt, sp = lb / (mt * nt);
-    const int r0 = rt * kFarTile, n0 = ct * kFarTile;
+    const int r0 = rt * TR, n0 = ct * TC;
     // taps that reach a row of the tile: r + shift in [0, M) for some r
     const int dir = ADJ ? 1 : -1;
     int t0 = 0, t1 = ntap;
     while (t0 < t1) {
         const long long s = (long long)dir * (m_lo + t0) * B;
-        if (r0 + s < M && r0 + kFarTile + s > 0) break;
+        if (r0 + s < M && r0 + TR + s > 0) break;
         ++t0;
     }
     while (t1 > t0) {
         const long long s = (long long)dir * (m_lo + t1 - 1) * B;
-        if (r0 + s < M && r0 + kFarTile + s > 0) break;
+        if (r0 + s < M && r0 + TR + s > 0) break;
         --t1;
     }
     const int nta = t1 - t0, nk = (K + kFarK - 1) / kFarK;
     const long long steps = (long long)nk * nta;
     const long long s0 = steps * sp / nsplit, s1 = steps * (sp + 1) / nsplit;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = (wave & 1) * 32, wc = (wave >> 1) * 32;
-    dx4 re[2][2], im[2][2], re2[2][2], im2[2][2];
+    const int wr = (NJ == 1 ? wave : wave & 1) * 32, wc = NJ == 1 ? 0 : (wave >> 1) * 32;
+    dx4 re[2][NJ], im[2][NJ], re2[2][NJ], im2[2][NJ];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) re[i][j] = im[i][j] = re2[i][j] = im2[i][j] = dx4{0, 0, 0, 0};
-    zd ga[2], gb[2];
+        for (int j = 0; j < NJ; ++j) re[i][j] = im[i][j] = re2[i][j] = im2[i][j] = dx4{0, 0, 0, 0};
+    zd ga[LA], gb[2];
     // the step being loaded: 8 kk from kk0, one tap
     int kk0 = nta > 0 ? (int)(s0 / nta) * kFarK : 0, tap = nta > 0 ? t0 + (int)(s0 % nta) : 0;
     auto load = [&]() {
         const long long sh = (long long)dir * (m_lo + tap) * B;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < LA; ++i) {
             const int row = (tid >> 3) + 32 * i, kk = kk0 + (tid & 7);
             const long long r = r0 + row + sh;
             ga[i] = (r >= 0 && r < M && kk < K) ? A[(size_t)r * K + kk] : zd{0, 0};
+        }
+#pragma unroll
+        for (int i = 0; i < NJ; ++i) {
             if constexpr (ADJ) {
                 const int kf = kk0 + (tid >> 6) + 4 * i, n = n0 + lane;
                 gb[i] = (kf < K && n < N) ? conjz(F[((size_t)tap * K + kf) * N + n]) : zd{0, 0};
             } else {
-                const int n = n0 + row;
-                gb[i] = (n < N && kk < K) ? F[((size_t)tap * N + n) * K + kk] : zd{0, 0};
+                const int row = (tid >> 3) + 32 * i, kk = kk0 + (tid & 7), n = n0 + row;
+                gb[i] = (row < TC && n < N && kk < K) ? F[((size_t)tap * N + n) * K + kk] : zd{0, 0};
             }
         }
         if (++tap == t1) {
@@ -243,11 +252,12 @@ __global__ void __launch_bounds__(256, 2) k_far_gemm(const zd* __restrict__ A, c
     };
     auto put = [&](int buf) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            sA[buf][((tid >> 3) + 32 * i) * LD + (tid & 7)] = ga[i];
+        for (int i = 0; i < LA; ++i) sA[buf][((tid >> 3) + 32 * i) * LD + (tid & 7)] = ga[i];
+#pragma unroll
+        for (int i = 0; i < NJ; ++i) {
             if constexpr (ADJ)
                 sB[buf][lane * LD + (tid >> 6) + 4 * i] = gb[i];
-            else
+            else if (NJ == 2 || tid < 8 * TC)
                 sB[buf][((tid >> 3) + 32 * i) * LD + (tid & 7)] = gb[i];
         }
     };
@@ -264,28 +274,29 @@ __global__ void __launch_bounds__(256, 2) k_far_gemm(const zd* __restrict__ A, c
         for (int h = 0; h < kFarK / 4; ++h) {
             // lane l holds row (column) l % 16 and kk = l / 16 of each 16 x 4 piece
             const int kk = 4 * h + (lane >> 4);
-            zd a[2], b[2];
+            zd a[2], b[NJ];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) a[i] = sA[buf][(wr + 16 * i + (lane & 15)) * LD + kk];
+#pragma unroll
+            for (int i = 0; i < NJ; ++i) b[i] = sB[buf][(wc + 16 * i + (lane & 15)) * LD + kk];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                a[i] = sA[buf][(wr + 16 * i + (lane & 15)) * LD + kk];
-                b[i] = sB[buf][(wc + 16 * i + (lane & 15)) * LD + kk];
-            }
+                if (NJ == 1 && r0 + wr + 16 * i >= M) continue;
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < NJ; ++j) {
                     re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].x, re[i][j], 0, 0, 0);
                     im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].y, im[i][j], 0, 0, 0);
                     re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[i].y, b[j].y, re[i][j], 0, 0, 0);
                     im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, b[j].x, im[i][j], 0, 0, 0);
                 }
+            }
         }
         if (++since == kFlush) {
             since = 0;
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < NJ; ++j) {
                     re2[i][j] += re[i][j];
                     im2[i][j] += im[i][j];
                     re[i][j] = im[i][j] = dx4{0, 0, 0, 0};
@@ -299,7 +310,7 @@ __global__ void __launch_bounds__(256, 2) k_far_gemm(const zd* __restrict__ A, c
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 // element v of a lane: row 4 v + l / 16, column l % 16
