@@ -374,8 +374,12 @@ int launch_l4(etaim_ctx* c, bool lf, dim3 grid, const cplx<R>* in, cplx<R>* out,
     return lf ? launch_l4<R, A, B, true, false>(c, grid, in, out, tw, a)
               : launch_l4<R, A, B, false, false>(c, grid, in, out, tw, a);
 }
-// the register x-line instances of xline_n
-#define ETAIM_XLINES(X) X(16) X(18) X(24) X(27) X(32) X(36) X(48)
+// the register x-line instances: those that x_engine 1 selects, and those that
+// x_engine 0 takes too (xreg)
+#define ETAIM_XLINES_1(X) X(16) X(24) X(48)
+#define ETAIM_XLINES_0(X) X(18) X(27) X(32) X(36)
+#define ETAIM_XLINES(X) ETAIM_XLINES_1(X) ETAIM_XLINES_0(X)
+#define ETAIM_IS_N(N) || n == N
 // the four-step instances of lines4_split
 #define ETAIM_L4_SPLITS(X) X(8, 12) X(6, 18) X(8, 16) X(12, 12) X(8, 24) X(12, 24) X(16, 24) X(24, 24)
 
@@ -421,26 +425,26 @@ int launch_lines(etaim_ctx* c, const cplx<R>* in, cplx<R>* out, const cplx<R>* t
 // N of the register x-line kernels (N_x = N with a register codelet), 0 if none
 int xline_n(const etaim_ctx* c) {
     const int n = c->gd.N[0];
-    if (c->gd.L[0] != 2 * n) return 0;
-    return (n == 16 || n == 18 || n == 24 || n == 27 || n == 32 || n == 36 || n == 48) ? n : 0;
-}
-
-// x_engine 1 can be set: N_x in {16, 24, 48}, or four-step lines of length
-// L_x = 2 N_x (the anterpolated grid is then transformed by them)
-bool xreg_ok(const etaim_ctx* c) {
-    const int n = c->gd.N[0];
-    if (n == 16 || n == 24 || n == 48) return true;
-    int A = 0, B = 0;
-    return n != 54 && n != 64 && lines4_split(c->gd.L[0], A, B);
+    return c->gd.L[0] == 2 * n && (false ETAIM_XLINES(ETAIM_IS_N)) ? n : 0;
 }
 
 // x_engine 0 takes the register x stage as well where it has lines for this
-// grid (18, 27, 32, 36 as register codelets, 54 and 64 as four-step lines):
-// the LDS-staged lines with the gather fused in took 54 + 19 us for 5 columns
-// of an 18^3 grid in FP64 (level-3 sphere), the register stage 15 + 5 us
-bool xreg(const etaim_ctx* c) {
+// grid (ETAIM_XLINES_0 as register codelets, 54 and 64 as four-step lines): the
+// LDS-staged lines with the gather fused in took 54 + 19 us for 5 columns of an
+// 18^3 grid in FP64 (level-3 sphere), the register stage 15 + 5 us
+bool xreg_always(const etaim_ctx* c) {
     const int n = c->gd.N[0];
-    return c->x_engine == 1 || n == 18 || n == 27 || n == 32 || n == 36 || n == 54 || n == 64;
+    return false ETAIM_XLINES_0(ETAIM_IS_N) || n == 54 || n == 64;
+}
+bool xreg(const etaim_ctx* c) { return c->x_engine == 1 || xreg_always(c); }
+
+// x_engine 1 can be set: ETAIM_XLINES_1, or four-step lines of length L_x =
+// 2 N_x (the anterpolated grid is then transformed by them), but not where
+// x_engine 0 takes the register stage anyway
+bool xreg_ok(const etaim_ctx* c) {
+    const int n = c->gd.N[0];
+    int A = 0, B = 0;
+    return (false ETAIM_XLINES_1(ETAIM_IS_N)) || (!xreg_always(c) && lines4_split(c->gd.L[0], A, B));
 }
 
 // N of the register quadrant kernels for this grid (N_y = N_z = N, N | 48
