@@ -23,10 +23,26 @@ def _torch():
     return torch
 
 
-def _dptr(t) -> int:
+def _dptr(t, n: int = 0) -> int:
+    """Address of a contiguous device tensor that holds at least n complex128
+    (the kernels take bare addresses and cannot check)."""
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("expected a contiguous device tensor")
+    if t.numel() * t.element_size() < 16 * n:
+        raise ValueError(f"expected at least {n} complex128 values, got {t.numel() * t.element_size()} bytes")
     return t.data_ptr()
+
+
+def _series(t, n: int):
+    """A time series t of at least n complex128 values; one that ends earlier
+    continues with zeros."""
+    torch = _torch()
+    if t.numel() >= n or t.dtype != torch.complex128 or not t.is_cuda or not t.is_contiguous():
+        return t  # (_dptr refuses what is left)
+    out = torch.zeros(n, dtype=torch.complex128, device=t.device)
+    out[:t.numel()] = t.detach().reshape(-1)
+    torch.cuda.current_stream().synchronize()  # the library works on its own stream
+    return out
 
 
 def _stats_dict(st: Stats, iters) -> dict:
@@ -91,27 +107,40 @@ class Problem:
         ph = np.ascontiguousarray(np.atleast_2d(phat), dtype=np.float64)
         V = out if out is not None else self.empty(self.nt, len(kh), self.ns)
         fn = _lib.load().etaim_excitation_planewave_noalloc if noalloc else _lib.load().etaim_excitation_planewave
+        if kh.shape != (len(kh), 3) or ph.shape != kh.shape:
+            raise ValueError("khat and phat need the same shape [B][3]")
         _lib.check(fn(self._h, len(kh), kh.ctypes.data_as(POINTER(c_double)), ph.ctypes.data_as(POINTER(c_double)),
-                      sigma, td, c_void_p(_dptr(V))))
+                      sigma, td, c_void_p(_dptr(V, self.nt * len(kh) * self.ns))))
         return V
 
+    def _rows(self, steps: int) -> int:
+        """Values of the first `steps` time steps (all of them at most)."""
+        return min(max(steps, 0), self.nt) * self.batch * self.ns
+
     def march(self, V, out=None, nsteps: int = 0):
+        """Forward march of the first nsteps time steps (0: all N_t).  V and
+        out are [N_t][B][ns] device arrays; a V that ends before the last step
+        continues with zeros."""
         I = out if out is not None else self.empty(self.nt, self.batch, self.ns)
+        n = self._rows(nsteps if nsteps > 0 else self.nt)
+        V = _series(V, n)
         it = np.zeros(self.nt, dtype=np.int32)
         st = Stats()
         st.iters_per_step = it.ctypes.data_as(POINTER(c_int32))
-        _lib.check(_lib.load().etaim_march(self._h, c_void_p(_dptr(V)), c_void_p(_dptr(I)), nsteps, byref(st)))
+        _lib.check(_lib.load().etaim_march(self._h, c_void_p(_dptr(V, n)), c_void_p(_dptr(I, n)), nsteps, byref(st)))
         return I, _stats_dict(st, it)
 
     def march_continue(self, V, I, first: int, nsteps: int):
         """Steps first .. first + nsteps - 1 of the forward march, continuing
         the history of the last march on this problem (or a loaded state);
         I holds the earlier steps and receives these."""
-        it = np.zeros(nsteps, dtype=np.int32)
+        it = np.zeros(max(nsteps, 0), dtype=np.int32)
         st = Stats()
         st.iters_per_step = it.ctypes.data_as(POINTER(c_int32))
-        _lib.check(_lib.load().etaim_march_continue(self._h, c_void_p(_dptr(V)), c_void_p(_dptr(I)), first, nsteps,
-                                                    byref(st)))
+        n = self._rows(first + nsteps)
+        V = _series(V, n)
+        _lib.check(_lib.load().etaim_march_continue(self._h, c_void_p(_dptr(V, n)), c_void_p(_dptr(I, n)), first,
+                                                    nsteps, byref(st)))
         return I, _stats_dict(st, it)
 
     def save_state(self) -> np.ndarray:
@@ -131,31 +160,46 @@ class Problem:
         it = np.zeros(self.nt, dtype=np.int32)
         st = Stats()
         st.iters_per_step = it.ctypes.data_as(POINTER(c_int32))
-        _lib.check(_lib.load().etaim_adjoint_march(self._h, c_void_p(_dptr(S)), c_void_p(_dptr(L)), byref(st)))
+        n = self._rows(self.nt)
+        S = _series(S, n)
+        _lib.check(_lib.load().etaim_adjoint_march(self._h, c_void_p(_dptr(S, n)), c_void_p(_dptr(L)), byref(st)))
         return L, _stats_dict(st, it)
 
     def apply_z(self, m: int, x):
         y = self.empty(*x.shape)
-        _lib.check(_lib.load().etaim_apply_z(self._h, m, c_void_p(_dptr(x)), c_void_p(_dptr(y))))
+        n = self.batch * self.ns
+        _lib.check(_lib.load().etaim_apply_z(self._h, m, c_void_p(_dptr(x, n)), c_void_p(_dptr(y, n))))
         return y
 
     def delayed_field(self, hist):
         b = self.empty(self.batch, self.ns)
-        _lib.check(_lib.load().etaim_delayed_field(self._h, c_void_p(_dptr(hist)), c_void_p(_dptr(b))))
+        n = self.info["ng"] * self.batch * self.ns
+        _lib.check(_lib.load().etaim_delayed_field(self._h, c_void_p(_dptr(hist, n)), c_void_p(_dptr(b))))
         return b
 
-    def farfield(self, dirs, I):
+    @staticmethod
+    def _dirs(dirs):
         d = np.ascontiguousarray(np.atleast_2d(dirs), dtype=np.float64)
+        if d.shape != (len(d), 3):
+            raise ValueError("directions need the shape [nd][3]")
+        return d
+
+    def farfield(self, dirs, I):
+        d = self._dirs(dirs)
         U = self.empty(self.nt, self.batch, len(d), 3)
+        n = self._rows(self.nt)
+        I = _series(I, n)
         _lib.check(_lib.load().etaim_farfield(self._h, len(d), d.ctypes.data_as(POINTER(c_double)),
-                                              c_void_p(_dptr(I)), c_void_p(_dptr(U))))
+                                              c_void_p(_dptr(I, n)), c_void_p(_dptr(U))))
         return U
 
     def farfield_adjoint(self, dirs, U):
-        d = np.ascontiguousarray(np.atleast_2d(dirs), dtype=np.float64)
+        d = self._dirs(dirs)
         S = self.empty(self.nt, self.batch, self.ns)
+        n = self.nt * self.batch * len(d) * 3
+        U = _series(U, n)
         _lib.check(_lib.load().etaim_farfield_adjoint(self._h, len(d), d.ctypes.data_as(POINTER(c_double)),
-                                                      c_void_p(_dptr(U)), c_void_p(_dptr(S))))
+                                                      c_void_p(_dptr(U, n)), c_void_p(_dptr(S))))
         return S
 
     def rcs(self, U, pol, df, pulse_sigma: float):
@@ -164,12 +208,13 @@ class Problem:
         Gaussian pulse of width pulse_sigma; pol [nd][3] (theta-hat for
         sigma_theta-theta)."""
         torch = _torch()
-        p = np.ascontiguousarray(np.atleast_2d(pol), dtype=np.float64)
+        p = self._dirs(pol)
         f = np.ascontiguousarray(np.atleast_1d(df), dtype=np.float64)
         out = torch.empty((len(f), self.batch, len(p)), dtype=torch.float64, device=U.device)
         _lib.check(_lib.load().etaim_rcs(self._h, len(p), p.ctypes.data_as(POINTER(c_double)), len(f),
                                          f.ctypes.data_as(POINTER(c_double)), float(pulse_sigma),
-                                         c_void_p(_dptr(U)), c_void_p(out.data_ptr())))
+                                         c_void_p(_dptr(U, self.nt * self.batch * len(p) * 3)),
+                                         c_void_p(out.data_ptr())))
         return out
 
     _EXPORT = {"lambda": (0, np.float64, lambda i: (i["ns"], 4, 64)),
