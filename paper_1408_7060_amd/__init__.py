@@ -28,8 +28,8 @@ def _dptr(t, n: int = 0) -> int:
     (the kernels take bare addresses and cannot check)."""
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("expected a contiguous device tensor")
-    if t.numel() * t.element_size() < 16 * n:
-        raise ValueError(f"expected at least {n} complex128 values, got {t.numel() * t.element_size()} bytes")
+    if t.nbytes < 16 * n:
+        raise ValueError(f"expected at least {n} complex128 values, got {t.nbytes} bytes")
     return t.data_ptr()
 
 
@@ -167,8 +167,7 @@ class Problem:
 
     def apply_z(self, m: int, x):
         y = self.empty(*x.shape)
-        n = self.batch * self.ns
-        _lib.check(_lib.load().etaim_apply_z(self._h, m, c_void_p(_dptr(x, n)), c_void_p(_dptr(y, n))))
+        _lib.check(_lib.load().etaim_apply_z(self._h, m, c_void_p(_dptr(x, self.batch * self.ns)), c_void_p(_dptr(y))))
         return y
 
     def delayed_field(self, hist):
